@@ -77,7 +77,8 @@ Layout layout_of(const Shape& s) {
     L.nres = take(4);
     L.perm = take(T * k * 4);
     L.inv = take(T * k * 4);
-    L.part = take((size_t)saem::router_slices(s) * 64 * E * 4);
+    // decode: the router's partial scores; bf16 prefill: the tiled FFN's claim counters
+    L.part = take(std::max((size_t)saem::router_slices(s) * 64 * E * 4, saem::ffn_tile_claim_bytes(s)));
     L.act = take((size_t)saem::ffn_act_rows(s) * L.Fa * (s.bf16 ? 2 : 4));
     L.xg = take((size_t)saem::ffn_gather_rows(s) * H * 2);
     L.meta = take(saem::ffn_tile_meta_bytes(s));
@@ -192,6 +193,7 @@ moe_status moe_grouped_ffn(const moe_dims* dims, const void* x, const int32_t* p
     a.act = at<char>(ws, L.act);
     a.xg = at<char>(ws, L.xg);
     a.tmeta = at<int32_t>(ws, L.meta);
+    a.tclaim = at<int32_t>(ws, L.part);
     a.Fa = L.Fa;
     a.ks = L.ks;
     a.y_ks_stride = L.rows * (long long)s.H;
@@ -302,6 +304,7 @@ static moe_status layer_forward(const moe_layer_args* a, void* ws, size_t ws_byt
     f.act = at<char>(ws, L.act);
     f.xg = at<char>(ws, L.xg);
     f.tmeta = at<int32_t>(ws, L.meta);
+    f.tclaim = at<int32_t>(ws, L.part);
     f.Fa = L.Fa;
     const bool y16 = saem::ffn_y_bf16(s);
     f.y = at<float>(ws, L.y);

@@ -35,15 +35,15 @@
 //    repack's outputs for phase 2 and the combine, and phase 2's trailing
 //    workgroups pack the offloaded rows.  That saves the repack's launch and
 //    its chain of dependent memory round trips before the weights start to flow.
-//  * tiled   (bf16, T > 64, prefill): 256 x 256 output tiles (eight waves of
-//    128 x 64 on MFMA 32x32x16) that one workgroup per CU works through in
-//    turn, both operands read as 1 KB tile-layout blocks by direct global->LDS
-//    loads through a five-stage ring; a token gather first copies the resident
-//    groups' rows into that layout, and phase 1 writes the activations in it;
+//  * tiled   (bf16, T > 64, prefill): output tiles of 128 weight rows x up to 256 rows
+//    of a group (four waves on MFMA 16x16x32), two persistent workgroups per CU that
+//    claim items from a queue per XCD, both operands read as 1 KB tile-layout blocks by
+//    direct global->LDS loads through a ring of stages; a token gather first copies the
+//    resident groups' rows into that layout, and phase 1 writes the activations in it;
 //    the expert outputs are bf16.
 // Both read counts and offsets from device memory: the stream kernel's grid is
 // sized for the worst case on the host and surplus workgroups exit at once; the
-// tiled kernel runs one workgroup per CU.
+// tiled kernel runs two workgroups per CU.
 #include <type_traits>
 
 #include "block_ops.hpp"
@@ -52,6 +52,8 @@
 
 namespace saem {
 namespace {
+
+constexpr int kTClaimPitch = 4;  // int32 words between two claim counters
 
 struct Args {
     int T, H, E, F, k, S, Fs, slots;
@@ -82,6 +84,7 @@ struct Args {
     void* xg;         // bf16 prefill: gathered token rows in the tile layout
     int32_t* tmeta;   // bf16 prefill: item tables of the tiled kernels
     int tcap1;        // capacity of the phase-1 table
+    int32_t* tclaim;  // bf16 prefill: claim counters of the tiled kernels, eight per phase
     uint16_t* y16;    // bf16 prefill: expert outputs [rows][H] in bf16 (instead of y)
     // decode with the repacking in phase 1 (fused): the ids, and the repack's outputs
     int fused;
@@ -275,10 +278,6 @@ __device__ Group routed_group_of(const Args& a, int rb, int c, int slot_, size_t
     g.w13 = static_cast<const uint8_t*>(a.w13) + slot * 2 * a.F * a.H * elt;
     g.w2 = static_cast<const uint8_t*>(a.w2) + slot * a.H * a.F * elt;
     return g;
-}
-
-__device__ Group routed_group(const Args& a, int e, size_t elt) {
-    return routed_group_of(a, a.seg_start[e], a.counts[e], a.expert_slot[e], elt);
 }
 
 __device__ Group shared_group(const Args& a, int s, size_t elt) {
@@ -676,152 +675,197 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
 // tiled kernel (prefill)
 // ---------------------------------------------------------------------------
 //
-// One item = one 256 x 256 output tile of one group: 256 weight rows (phase 1:
-// 128 features, their gate and up rows; phase 2: 256 rows of W2) x 256 of the
-// group's rows.  Eight waves in 2 (rows) x 4 (tokens), each 128 rows x 64
-// tokens = 4 x 2 tiles of v_mfma_f32_32x32x16_bf16 (128 fp32 accumulators per
-// lane); a phase-1 wave holds the gate and the up rows of the same 64 features,
-// so SwiGLU runs in registers.  Waves 0-3 and 4-7 form two groups with one wave
-// of each on every SIMD; wave w has rows w % 2 and token quarter 2 ((w / 2) % 2)
-// + w / 4, so a group's end past its first 64 rows keeps both groups busy.  A
-// wave whose 64 tokens all lie past the group's end skips its MFMAs.
-//
-// Schedule (ping-pong): the K loop runs in half-slab phases with a barrier after
-// each.  While one wave group reads a slab's operand fragments from LDS (and
-// issues its next loads), the other multiplies the slab before, so a SIMD's
-// MFMA pipe and the CU's LDS work at once instead of every wave reading after
-// the same barrier and then multiplying (on operands already in LDS the
-// lockstep loop reaches about two thirds of the MFMA peak, this one about 0.9).
+// One item = 128 weight rows (phase 1: 64 features, their gate and up rows; phase 2: 128
+// rows of W2) x up to 256 of a group's rows.  Four waves in 2 (weight rows) x 2 (tokens);
+// a wave holds 64 weight rows x every second 16-token block, so that a short item keeps
+// all of them busy; a phase-1 wave holds the gate and the up rows of the same 32
+// features, so SwiGLU runs in registers.  The tile runs at the number of token blocks
+// that the item has, rounded up to a multiple of four (four copies of the K loop): loads,
+// LDS reads and MFMAs for the rows past a group's end are left out.
 //
 // Operands: both are read as 1 KB blocks of the MFMA tile layout (16 rows x 32
 // columns; lane l's 16 bytes are row l % 16, columns 8 (l / 16) .. + 7): the
 // weights as they are stored, the tokens from a copy that the token gather
 // (k_gather_tokens) makes of the resident groups' rows, and phase 2's from the
-// activations, which phase 1 writes in that layout.  A CU fills its LDS about
-// three times faster from such contiguous blocks than from loads that gather
-// 64 bytes from each of 16 row-major token rows.
+// activations, which phase 1 writes in that layout.  Gathered 64-byte pieces of
+// row-major rows in their place filled the LDS at 14 TB/s against 19.
 //
-// K runs in 32-wide slabs through a ring of kGStages LDS stages (32 KB each:
-// 16 weight blocks, 16 token blocks) filled by direct global->LDS loads: one
-// wave instruction moves one 1 KB block, lane l's 16 bytes landing at byte
-// 16 l, so every MFMA operand is one conflict-free 16-byte LDS read per lane.
-// The loads are issued as inline assembly and waited for by count (the
-// compiler cannot see their LDS writes, so it does not make every LDS read wait
-// for all of them): each wave issues exactly four per slab and no other
-// vector-memory instruction in the K loop, so "slab kt has landed" is "at most
-// 4 x (slabs issued after kt) loads outstanding", then a barrier.  The ring is
-// the kernel's only LDS: up to kGStages - 1 slabs (128 KB) are in flight, which
-// is what the load latency under this traffic asks for.
+// K runs in 32-wide slabs through a ring of LDS stages filled by direct global->LDS
+// loads: one wave instruction moves one 1 KB block, lane l's 16 bytes landing at byte
+// 16 l, so every MFMA operand is one conflict-free 16-byte LDS read per lane.  The loads
+// are inline assembly and waited for by count: a wave issues L per slab and no other
+// vector-memory instruction in the K loop.  Fragments are double-buffered in registers:
+// while slab kt's MFMAs issue, slab kt + 1's fragments are read and slab kt + S goes out
+// over slab kt's stage, so a slab needs one barrier.
 //
-// Items come from a table the token gather writes (one scalar load per item);
-// group g owns (weight tiles) x ceil(rows / 256) items, weight tile major.  The
-// kernel is persistent, one workgroup per CU: the XCDs get equal contiguous
-// ranges of the real items (the hardware deals workgroups to the 8 XCDs
-// round-robin), which an XCD's workgroups take in turn, so its 32 CUs start
-// each round together on neighbouring tiles of one group and share its weight
-// and token panels in their L2.
+// What bounds it: on groups of many rows, the power limit -- the chip runs the K loop at
+// 1.4 to 1.8 GHz -- and the L2; hence the 16x16x32 MFMA, which on random operands alone
+// sustains 1.90 PFLOP/s against 1.65 for 32x32x16, and LDS reads and loads kept few.  On
+// groups of few rows, the weight stream from HBM and the last round of items.  Two
+// workgroups per CU let one's prologue and epilogue overlap the other's K loop; half the
+// weight rows of a 256 x 256 tile halve the last round.  Before (256 x 256 tiles, eight
+// waves on 32x32x16, one workgroup per CU) and now, phase 1 / phase 2 in us, bf16:
+//   64 experts x 1024 rows, H 2048, F 1408:   680 / 384 -> 618 / 363
+//   48 experts x  256 rows, H 2048, F 1408:   184 /  95 -> 161 /  91
+//   48 experts x  100 rows, H 2048, F 1408:   158 /  82 -> 128 /  69
+//   48 experts x   40 rows, H 2048, F 1408:   140 /  72 -> 108 /  66
+//    8 experts x   83 rows, H 4096, F 14336:  386 / 284 -> 352 / 169
+//   64 experts x   16 rows, H 2048, F 768:     93 /  50 ->  72 /  42
+// The weights of an item of up to 64 rows are loaded non-temporally (118 -> 108 us for
+// phase 1 at 40 rows a group, 79 -> 72 at 16; phase 2 63 -> 66 and 51 -> 42): they are read
+// once.  With more rows it gained nothing (128 -> 122 and 69 -> 80 us at 100 rows).
+//
+// Items come from tables that the token gather writes.  Workgroups start on items
+// 0, 1, ... and claim further ones from a counter per XCD (the hardware deals workgroups
+// to the 8 XCDs round-robin), then from the other XCDs' once theirs is used up, so that
+// items of unequal length even out.  An XCD takes chunks of kTChunk neighbouring items,
+// which share weight and token panels in its L2.  Which workgroup runs an item does not
+// change its result.
 
-constexpr int kGM = 256;          // weight rows per item
-constexpr int kGN = 256;          // group rows (tokens) per item
-constexpr int kGStages = 5;       // LDS ring
-constexpr int kGStageBytes = 32 * 1024;
+constexpr int kTR = 128;           // weight rows per item
+constexpr int kTF = kTR / 2;       // features per item in phase 1
+constexpr int kTN = 256;           // group rows (tokens) per item
+constexpr int kTB = 4;             // token tiles that consecutive items sweep together
+constexpr int kTChunk = 32;        // consecutive items an XCD takes together
+constexpr int kTLds = 80 * 1024;   // LDS of a workgroup: two workgroups per CU
+constexpr int kTabWgs = 16;        // workgroups of the token gather that write the item tables
 
-// One item of the tiled kernels (a single 32-byte scalar load).
-struct __attribute__((aligned(32))) TileItem {
+// Tables of the tiled kernels, written by the token gather into tmeta: int32 header[8]
+// (items of phase 1, of phase 2), TileGroup[groups], then one TileItem per item of
+// phase 1 and of phase 2.  All are read with scalar loads.
+struct __attribute__((aligned(16))) TileGroup {
     int32_t wsel;     // slot of the routed expert (>= 0), or -(s + 1) for shared expert s
     int32_t count;    // rows of the group
     int32_t rowbase;  // first row of the group in the packed row space (y)
-    int32_t Fg;       // expert width
-    int32_t xblk;     // first row block of the group's token rows in xg
-    int32_t ablk;     // first row block of the group's activations
-    int32_t wt;       // weight tile
-    int32_t n0;       // first group row of the tile
+    int32_t blk;      // first row block of the group's activations
 };
-// Tile metadata: int32 header[8] (items of phase 1, of phase 2), then
-// TileItem phase1[cap1], phase2[cap2].
+struct __attribute__((aligned(8))) TileItem {
+    uint32_t wt;      // weight tile
+    uint32_t gt;      // group | token tile << 9
+};
+constexpr int kTHeader = 8;
+constexpr int kTPitch = 136;       // phase 2's staged token rows, in elements
 
 typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
-// One direct global -> LDS load of 16 bytes per lane: lane l's bytes from g land
-// at LDS byte address lds + 16 l (lds is wave-uniform, passed through M0).
-__device__ __forceinline__ void lds_load_1k(uint32_t lds, const void* g) {
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "s_nop 0\n\t"
-        "global_load_lds_dwordx4 %1, off"
-        :
-        : "s"(lds), "v"(g)
-        : "memory", "m0");
+// One direct global -> LDS load of 16 bytes per lane: lane l's bytes from base + voff land
+// at LDS byte address lds + 16 l (lds and base are wave-uniform, lds passed through M0).
+template <bool kNt>
+__device__ __forceinline__ void lds_load_1k(uint32_t lds, const void* base, uint32_t voff) {
+    if constexpr (kNt)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds), "v"(voff), "s"(base)
+                     : "memory", "m0");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds), "v"(voff), "s"(base)
+                     : "memory", "m0");
 }
 
-// Wait until at most N of this wave's vector-memory loads are outstanding and its
-// LDS accesses are done, then a workgroup barrier.  The memory clobber keeps
-// the compiler's LDS accesses on their side of it.
+// Wait until at most N of this wave's vector-memory operations are outstanding and its LDS
+// accesses are done, then a workgroup barrier.  The wait is the builtin, so that the
+// compiler knows the LDS reads before it have landed and adds no waits of its own.
 template <int N>
 __device__ __forceinline__ void wait_then_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(N) : "memory");
+    static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+    asm volatile("s_barrier" : : : "memory");
 }
 
-__device__ __forceinline__ f32x16 mfma32x32x16(bf16x8 a, bf16x8 b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+// acc += A B (16 x 16 x 32), the accumulator tied in place.  Written out because the
+// compiler, given the builtin, picks another register for the result than for the addend
+// and fills the K loop with copies.  The caller keeps the waits that the compiler would
+// add between an MFMA and other uses of its accumulator.
+__device__ __forceinline__ void mfma_tied(f32x4& acc, bf16x8 a, bf16x8 b) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
-
-// Weight tiles of a group of width Fg: phase 1 covers 128 features per tile, phase 2 256 rows of W2.
-__device__ __forceinline__ int weight_tiles(const Args& a, int Fg, bool down) {
-    return down ? (a.H + kGM - 1) / kGM : (Fg + kGM / 2 - 1) / (kGM / 2);
+// Weight tiles of a group of width Fg: phase 1 covers 64 features per tile, phase 2 128 rows of W2.
+__host__ __device__ constexpr int weight_tiles(int H, int Fg, bool down) {
+    return down ? (H + kTR - 1) / kTR : (Fg + kTF - 1) / kTF;
 }
 
-// Writes both phases' item tables: the groups are the active resident routed
-// experts (s_list order, with their (segment start, count, slot) in s_info) and
-// then the S shared experts; s_bpre holds the routed groups' row-block prefix.
+// Writes the item tables of both phases (workgroups part = 0 .. parts - 1 share the
+// entries; part 0 also writes the groups, the item counts and clears the claim counters).
+// The groups -- the S shared experts and the active resident routed ones, with their
+// (segment start, count, slot) in s_info and their row-block prefix in s_bpre -- are
+// taken in order of falling row count, so that the long items start first.  Inside a group
+// the items go through blocks of kTB token tiles, weight tile by weight tile: consecutive
+// items share their weight and token panels.
 __device__ void write_tile_items(const Args& a, int nact, const int4* s_info, const int* s_bpre, int rb_routed,
-                                 int* s_ipre, int* s_tot) {
+                                 int* s_ipre, int* s_tot, int* s_rows, int16_t* s_ord, int part, int parts) {
     const int ng = nact + a.S;
     const int tb16 = (a.T + 15) / 16;
-    TileItem* tab = reinterpret_cast<TileItem*>(a.tmeta + 8);
+    const int P = a.T * a.k;
+    // group gi: shared expert gi for gi < S, else entry gi - S of the active list
+    for (int gi = threadIdx.x; gi < ng; gi += 256) {
+        int rows = a.T;
+        if (gi >= a.S) {
+            const int4 inf = s_info[gi - a.S];
+            rows = min(max(inf.y, 0), P - min(max(inf.x, 0), P));
+        }
+        s_rows[gi] = rows;
+    }
+    __syncthreads();
+    for (int gi = threadIdx.x; gi < ng; gi += 256) {
+        const int rows = s_rows[gi];
+        int rank = 0;
+        for (int o = 0; o < ng; ++o) {
+            const int r = s_rows[o];
+            rank += (r > rows || (r == rows && o < gi)) ? 1 : 0;
+        }
+        s_ord[rank] = (int16_t)gi;
+    }
+    __syncthreads();
+    TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);
+    if (part == 0) {
+        if (threadIdx.x < 2 * 8) a.tclaim[threadIdx.x * kTClaimPitch] = 0;
+        for (int o = threadIdx.x; o < ng; o += 256) {
+            const int gi = s_ord[o];
+            TileGroup g;
+            g.count = s_rows[gi];
+            if (gi < a.S) {
+                g.wsel = -(gi + 1);
+                g.rowbase = P + gi * a.T;
+                g.blk = rb_routed + gi * tb16;
+            } else {
+                const int4 inf = s_info[gi - a.S];
+                g.wsel = inf.z;
+                g.rowbase = min(max(inf.x, 0), P);
+                g.blk = s_bpre[gi - a.S];
+            }
+            groups[o] = g;
+        }
+    }
+    TileItem* tab = reinterpret_cast<TileItem*>(groups + a.max_routed + a.S);
     for (int ph = 0; ph < 2; ++ph) {
         const bool down = ph == 1;
-        const int total = group_prefix(ng, s_ipre, s_tot + ph, [&](int gi) {
-            const int rows = gi < nact ? max(s_info[gi].y, 0) : a.T;
-            const int Fg = gi < nact ? a.F : a.Fs;
-            return weight_tiles(a, Fg, down) * ((rows + kGN - 1) / kGN);
+        const int total = group_prefix(ng, s_ipre, s_tot + ph, [&](int o) {
+            const int gi = s_ord[o];
+            return weight_tiles(a.H, gi < a.S ? a.Fs : a.F, down) * ((s_rows[gi] + kTN - 1) / kTN);
         });
         TileItem* out = tab + (down ? a.tcap1 : 0);
-        for (int i = threadIdx.x; i < total; i += blockDim.x) {
+        for (int i = part * 256 + threadIdx.x; i < total; i += parts * 256) {
             int lo = 0, hi = ng - 1;  // last group with s_ipre[g] <= i
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (s_ipre[mid] <= i) lo = mid;
                 else hi = mid - 1;
             }
-            TileItem it;
-            if (lo < nact) {
-                const int4 inf = s_info[lo];
-                const int P = a.T * a.k;
-                const int rb = min(max(inf.x, 0), P);
-                it.wsel = inf.z;
-                it.count = min(max(inf.y, 0), P - rb);
-                it.rowbase = rb;
-                it.Fg = a.F;
-                it.xblk = s_bpre[lo];
-                it.ablk = s_bpre[lo];
-            } else {
-                const int sh = lo - nact;
-                it.wsel = -(sh + 1);
-                it.count = a.T;
-                it.rowbase = a.T * a.k + sh * a.T;
-                it.Fg = a.Fs;
-                it.xblk = rb_routed;
-                it.ablk = rb_routed + sh * tb16;
-            }
-            const int ntt = (it.count + kGN - 1) / kGN;
+            const int gi = s_ord[lo];
+            const int nwt = weight_tiles(a.H, gi < a.S ? a.Fs : a.F, down);
+            const int ntt = (s_rows[gi] + kTN - 1) / kTN;
             const int local = i - s_ipre[lo];
-            it.wt = local / ntt;
-            it.n0 = (local % ntt) * kGN;
+            const int tb = local / (nwt * kTB), rest = local - tb * nwt * kTB;
+            const int width = min(kTB, ntt - tb * kTB);
+            TileItem it;
+            it.wt = rest / width;
+            it.gt = (uint32_t)lo | (uint32_t)(tb * kTB + rest % width) << 9;
             out[i] = it;
         }
-        if (threadIdx.x == 0) a.tmeta[ph] = total;
+        if (part == 0 && threadIdx.x == 0) a.tmeta[ph] = total;
         __syncthreads();  // s_ipre is rewritten for the next phase
     }
 }
@@ -835,7 +879,7 @@ __device__ void write_tile_items(const Args& a, int nact, const int4* s_info, co
 //       RB = bpre[nact];
 //   act: the same for the routed groups; shared expert s at RB + s ceil(T / 16).
 // Block (rb, c) of a buffer with K columns starts at element (rb K / 32 + c) 512.
-// Workgroup 0 also writes the tiled kernels' item tables; the workgroups past
+// The first workgroups also write the tiled kernels' item tables; the workgroups past
 // the row blocks pack the offloaded rows.
 __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int blocks_max) {
     __shared__ int s_list[256];
@@ -843,6 +887,8 @@ __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int blocks_max) {
     __shared__ int s_wsum[8];
     __shared__ int s_bpre[257];
     __shared__ int s_ipre[kGMaxGroups + 1];
+    __shared__ int s_rows[kGMaxGroups];
+    __shared__ int16_t s_ord[kGMaxGroups];
     __shared__ int s_tok[16];
     const int pid = blockIdx.x;
     if (pid >= blocks_max) {
@@ -852,7 +898,9 @@ __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int blocks_max) {
     const int nact = list_active(a, s_list, s_wsum, s_info);
     const int rb_routed =
         group_prefix(nact, s_bpre, s_wsum + 4, [&](int gi) { return (max(s_info[gi].y, 0) + 15) / 16; });
-    if (pid == 0) write_tile_items(a, nact, s_info, s_bpre, rb_routed, s_ipre, s_wsum + 5);
+    const int parts = min(kTabWgs, blocks_max);
+    if (pid < parts)
+        write_tile_items(a, nact, s_info, s_bpre, rb_routed, s_ipre, s_wsum + 5, s_rows, s_ord, pid, parts);
     if (threadIdx.x < 16) {
         const int r = threadIdx.x;
         int t = -1;
@@ -898,224 +946,264 @@ __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int blocks_max) {
     }
 }
 
-// One workgroup per CU (the kernel's LDS admits one), looping over items.  tab: this
-// phase's item table, passed on its own and restrict-qualified, so that the compiler knows
-// the kernel's stores leave it alone and reads the descriptors through scalar loads (a
-// vector load would come with a wait for every outstanding memory operation).
+// Item of the q-th claim on XCD x's queue: the XCDs take chunks of kTChunk items in turn.
+__device__ __forceinline__ int claimed_item(int q, int x) {
+    return ((q / kTChunk) * 8 + x) * kTChunk + q % kTChunk;
+}
+
+// A persistent kernel, two workgroups per CU.  tab, groups: this phase's tables, passed on
+// their own and restrict-qualified, so that the compiler knows the kernel's stores leave
+// them alone and reads them through scalar loads.  claim: eight counters, one per XCD.
 template <bool kDown>
-__global__ void __launch_bounds__(512, 1) k_ffn_tiled(Args a, const TileItem* __restrict__ tab) {
-    __shared__ __attribute__((aligned(1024))) uint8_t sbuf[kGStages * kGStageBytes];
+__global__ void __launch_bounds__(256, 2)
+    k_ffn_tiled(Args a, const TileItem* __restrict__ tab, const TileGroup* __restrict__ groups, int32_t* claim) {
+    __shared__ __attribute__((aligned(1024))) uint8_t sbuf[kTLds];
+    int32_t* s_next = reinterpret_cast<int32_t*>(sbuf + kTLds - 16);  // free once the K loop is done
 
-    // XCD-aware order: XCD x = pid % 8 takes the real items [x per, (x + 1) per), which its
-    // workgroups take in turn: the CUs of an XCD start each round together on neighbouring
-    // tiles of one group and share its panels in their L2
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)sbuf;
+    const uint32_t off0 = 16 * lane;  // this lane's 16 bytes of a 1 KB block
     const int n_items = a.tmeta[kDown ? 1 : 0];
-    const int per = (n_items + 7) / 8;
-    const int xcd = blockIdx.x % 8;
-    const int xend = min((xcd + 1) * per, n_items);
-    const int step = gridDim.x / 8;
-    int item = xcd * per + (int)(blockIdx.x / 8);
-    TileItem nxt = tab[item < xend ? item : 0];  // the next item's descriptor, loaded one item ahead
-    for (; item < xend; item += step) {
-        __syncthreads();  // the previous item's epilogue is done with the LDS
-        const TileItem it = nxt;
-        if (item + step < xend) nxt = tab[item + step];
+    const int q0 = gridDim.x / 8;  // claims up to here are the workgroups' first items
+    int xcd = blockIdx.x % 8;
+    int item = claimed_item(blockIdx.x / 8, xcd);
 
-        const int tid = threadIdx.x, lane = lane_id();
-        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int grp = wave >> 2;  // wave group
-        const int wm = wave & 1, wn = 2 * ((wave >> 1) & 1) + grp;
-        const int K = kDown ? it.Fg : a.H;
-        const int nk = K / 32;  // slabs
-        const size_t wsize = (size_t)(kDown ? 1 : 2) * it.Fg * a.H;  // elements of one expert's matrix
-        const uint16_t* wbase;
-        if (it.wsel >= 0) wbase = static_cast<const uint16_t*>(kDown ? a.w2 : a.w13) + (size_t)it.wsel * wsize;
-        else wbase = static_cast<const uint16_t*>(kDown ? a.ws2 : a.ws13) + (size_t)(-it.wsel - 1) * wsize;
-        // phase 1: features r0 .. r0 + 127 (gate rows in LDS blocks 0..7, up rows in 8..15);
-        // phase 2: rows r0 .. r0 + 255 of W2
-        const int r0 = it.wt * (kDown ? kGM : kGM / 2);
-        const int rows_out = kDown ? a.H : it.Fg;  // rows (phase 2) or features (phase 1) that exist
-        const int n0 = it.n0;
+    // the next item of XCD queue xcd, or of another queue once that one is empty; -1 when all
+    // are.  By wave 0; the counters only grow, so the loop ends.
+    auto steal = [&]() -> int {
+        for (;;) {
+            const int x = (xcd + (lane & 7)) & 7;
+            const int q = __hip_atomic_load(claim + x * kTClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long some = __ballot(lane < 8 && claimed_item(q0 + q, x) < n_items);
+            if (!some) return -1;
+            xcd = (xcd + __ffsll((long long)some) - 1) & 7;
+            int got = 0;
+            if (lane == 0)
+                got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
+            if (it < n_items) return it;
+        }
+    };
+    if (item >= n_items) {
+        if (wave == 0) {
+            const int it = steal();
+            if (lane == 0) *s_next = it;
+        }
+        __syncthreads();
+        item = __builtin_amdgcn_readfirstlane(*s_next);
+        __syncthreads();
+    }
 
-        // 16-row tile of the weight matrix held in LDS weight block b; a block past the
-        // matrix reads tile 0 instead (its rows are never stored)
-        auto row_tile = [&](int b) -> int {
-            if (kDown) {
-                const int rt = r0 / 16 + b;
-                return 16 * rt < a.H ? rt : 0;
-            }
-            const int f16 = r0 / 16 + (b & 7);
-            if (16 * f16 >= it.Fg) return 0;
-            return b < 8 ? f16 : it.Fg / 16 + f16;
-        };
-        // this wave's loads: weight blocks 2w, 2w + 1 and token blocks 2w, 2w + 1; a token
-        // block past the group reads the group's first block instead (never stored)
-        const uint16_t* gW0 = wbase + (size_t)row_tile(2 * wave) * nk * 512 + lane * 8;
-        const uint16_t* gW1 = wbase + (size_t)row_tile(2 * wave + 1) * nk * 512 + lane * 8;
-        const uint16_t* gX[2];
+    while (item >= 0) {
+        const TileItem ti = tab[item];
+        const TileGroup tg = groups[ti.gt & 511];
+        const int n0 = (int)(ti.gt >> 9) * kTN;  // first group row of the item
+        const bool shared = tg.wsel < 0;
+        const int Fg = shared ? a.Fs : a.F;
+        const int K = kDown ? Fg : a.H;
+        const int nk = K / 32;  // slabs (even: H and the widths are multiples of 64)
+        // phase 1: features r0 .. r0 + 63 (gate rows in LDS blocks 0..3, up rows in 4..7);
+        // phase 2: rows r0 .. r0 + 127 of W2
+        const int r0 = (int)ti.wt * (kDown ? kTR : kTF);
+        const size_t wsize = (size_t)(kDown ? 1 : 2) * Fg * a.H;  // elements of one expert's matrix
+        const uint16_t* wbase = shared ? static_cast<const uint16_t*>(kDown ? a.ws2 : a.ws13) + (size_t)(-tg.wsel - 1) * wsize
+                                       : static_cast<const uint16_t*>(kDown ? a.w2 : a.w13) + (size_t)tg.wsel * wsize;
+        // this wave's weight blocks: wave and 4 + wave.  A row tile past the matrix (H not a
+        // multiple of 128) reads tile 0 instead: its rows are never stored
+        const uint16_t* gw[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int nb = n0 / 16 + 2 * wave + i;
-            const int blk = (16 * nb < it.count) ? nb : 0;
-            if (!kDown)
-                gX[i] = static_cast<const uint16_t*>(a.xg) + (size_t)(it.xblk + blk) * (a.H / 32) * 512 + lane * 8;
-            else
-                gX[i] = static_cast<const uint16_t*>(a.act) + (size_t)(it.ablk + blk) * (a.Fa / 32) * 512 + lane * 8;
+            int rt;
+            if (kDown) {
+                rt = r0 / 16 + 4 * i + wave;
+                if (16 * rt >= a.H) rt = 0;
+            } else {
+                rt = i * (Fg / 16) + r0 / 16 + wave;
+            }
+            gw[i] = wbase + (size_t)rt * nk * 512;
         }
-        const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)sbuf;
-        auto issue = [&](int kt, int stage) {
-            const uint32_t base = lds0 + stage * kGStageBytes;
-            lds_load_1k(base + (2 * wave) * 1024, gW0 + (size_t)kt * 512);
-            lds_load_1k(base + (2 * wave + 1) * 1024, gW1 + (size_t)kt * 512);
-            lds_load_1k(base + (16 + 2 * wave) * 1024, gX[0] + (size_t)kt * 512);
-            lds_load_1k(base + (17 + 2 * wave) * 1024, gX[1] + (size_t)kt * 512);
-        };
+        // first block of the group's token operand, and the elements of one row block
+        const int kx = kDown ? a.Fa : a.H;
+        const int xblk = (!kDown && shared) ? tg.blk - (-tg.wsel - 1) * ((a.T + 15) / 16) : tg.blk;
+        const uint16_t* xbase = static_cast<const uint16_t*>(kDown ? a.act : a.xg) + (size_t)xblk * (kx / 32) * 512;
+        const int nblk = min(kTN / 16, (tg.count - n0 + 15) / 16);  // token blocks of the item
 
-        // operand blocks of this wave: A tile m (32 rows) = LDS weight blocks ab[m], ab[m] + 1;
-        // phase 1: m = 0, 1 gate rows, m = 2, 3 the up rows of the same features
-        int ab[4];
+        // the item with its tokens in NB blocks (4, 8, 12 or 16)
+        auto run = [&](auto nb_tag) {
+            constexpr int NB = decltype(nb_tag)::value;
+            constexpr int NF = NB / 2;            // token fragments of a wave: blocks 2 n + wn
+            constexpr int L = (8 + NB) / 4;       // loads of a wave per slab
+            constexpr int kSlab = (8 + NB) * 1024;
+            constexpr int S = NB == 4 ? 6 : kTLds / kSlab;  // stages of the ring
+            static_assert(S * kSlab <= kTLds && (S - 1) * L < 64, "ring");
+            constexpr bool kNtW = NB == 4;        // weights loaded non-temporally
+            uint32_t off = off0;  // opaque: its uses' sums are made here, not kept across the items
+            asm volatile("" : "+v"(off));
+            // a token block past the group reads the group's first block instead (never stored)
+            const uint16_t* gx[NB / 4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m)
-            ab[m] = kDown ? 8 * wm + 2 * m : (m < 2 ? 4 * wm + 2 * m : 8 + 4 * wm + 2 * (m - 2));
-        // B tile jn (32 tokens) = token blocks 16 + 4 wn + 2 jn (+1).  Lane's 16-byte piece of a
-        // 32-row (or 32-token) operand at K step s of the slab: block + (l % 32) / 16, piece
-        // (l % 16) + 16 (2 s + l / 32)
-        const int half = (lane >> 4) & 1;
-        const int piece0 = (lane & 15) + 16 * (lane >> 5);
-        // a wave whose rows or tokens all lie past the group skips its MFMAs
-        const bool live = (n0 + 64 * wn < it.count) && (r0 + (kDown ? 128 : 64) * wm < rows_out);
+            for (int i = 0; i < NB / 4; ++i) {
+                const int tb = 4 * i + wave;
+                gx[i] = xbase + (size_t)(tb < nblk ? n0 / 16 + tb : 0) * (kx / 32) * 512;
+            }
+            auto load = [&](int i, int kt, int stage) {
+                const uint32_t to = lds0 + stage * kSlab + (4 * i + wave) * 1024;
+                if (i < 2) lds_load_1k<kNtW>(to, gw[i < 2 ? i : 0] + (size_t)kt * 512, off);
+                else lds_load_1k<false>(to, gx[i < 2 ? 0 : i - 2] + (size_t)kt * 512, off);
+            };
+            auto rd = [&](int stage, int b) {
+                return __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sbuf + stage * kSlab + b * 1024 + off));
+            };
+            // weight fragment m: phase 1: m = 0, 1 gate rows, m = 2, 3 the up rows of the same features
+            auto ablk = [&](int m) { return kDown ? 4 * wm + m : (m < 2 ? 2 * wm + m : 4 + 2 * wm + m - 2); };
 
-        f32x16 acc[4][2];
+            f32x4 acc[NF][4];
 #pragma unroll
-        for (int m = 0; m < 4; ++m)
+            for (int n = 0; n < NF; ++n)
 #pragma unroll
-            for (int jn = 0; jn < 2; ++jn) acc[m][jn] = f32x16{};
+                for (int m = 0; m < 4; ++m) acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+            bf16x8 A[2][4], B[2][NF];
 
-        // Phases: in phase 2 kt group 0 reads slab kt's fragments, then issues its loads of
-        // slab kt + D, while group 1 multiplies slab kt - 1; in phase 2 kt + 1 group 0
-        // multiplies slab kt while group 1 reads it and issues its loads of slab kt + D.  The
-        // barrier closing an odd phase 2 kt + 1 also waits for every wave's loads of slab kt + 1.
-        // Slab kt + D goes to the stage of slab kt - 1, which both groups have read in phases
-        // 2 kt - 2 and 2 kt - 1.  Both groups pass 2 nk + 2 barriers.
-        constexpr int D = kGStages - 1;
 #pragma unroll
-        for (int st = 0; st < D; ++st)
-            if (st < nk) issue(st, st);
-        auto wait_slab = [&](int n) {  // n: slabs this wave may still have in flight
-            __builtin_amdgcn_sched_barrier(0);
-            if (n >= 3) wait_then_barrier<12>();
-            else if (n == 2) wait_then_barrier<8>();
-            else if (n == 1) wait_then_barrier<4>();
-            else wait_then_barrier<0>();
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        auto bar_lds = [&]() {  // end of a phase that needs no load to have landed
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        wait_slab(min(D - 1, nk - 1));  // slab 0
-        if (grp == 1) bar_lds();        // phase 0: group 1 has no slab to multiply yet
-        int stage = 0;
-        for (int kt = 0; kt < nk; ++kt) {
-            bf16x8 A[2][4], B[2][2];
-            if (live) {
-                const uint8_t* sp = sbuf + stage * kGStageBytes;
+            for (int st = 0; st < S; ++st)
+                if (st < nk) {
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const int off = 16 * (piece0 + 32 * ks) + 1024 * half;
-#pragma unroll
-                    for (int m = 0; m < 4; ++m)
-                        A[ks][m] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sp + ab[m] * 1024 + off));
-#pragma unroll
-                    for (int jn = 0; jn < 2; ++jn)
-                        B[ks][jn] = __builtin_bit_cast(
-                            bf16x8, *reinterpret_cast<const u32x4*>(sp + (16 + 4 * wn + 2 * jn) * 1024 + off));
+                    for (int i = 0; i < L; ++i) load(i, st, st);
                 }
-            }
-            if (kt + D < nk) issue(kt + D, stage == 0 ? D : stage - 1);
-            const int left = min(D - 1, nk - 2 - kt);  // slabs past kt + 1 this wave has in flight
-            if (grp == 0) bar_lds();
-            else wait_slab(left);
-            if (live) {
+            if (nk >= S) wait_then_barrier<(S - 1) * L>();
+            else wait_then_barrier<0>();
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks)
+            for (int m = 0; m < 4; ++m) A[0][m] = rd(0, ablk(m));
 #pragma unroll
-                    for (int m = 0; m < 4; ++m)
+            for (int n = 0; n < NF; ++n) B[0][n] = rd(0, 8 + 2 * n + wn);
+            asm volatile("s_nop 7" ::: "memory");
+
+            // Slab kt: its fragments are in registers (set P).  Once slab kt + 1 has landed
+            // everywhere, read its fragments and load slab kt + S over slab kt, spread
+            // between the MFMAs.  Past the last slab the read returns stale LDS, unused.
+            int stage = 0;
+            auto slab = [&](auto p_tag, auto tail_tag, int kt) {
+                constexpr int P = decltype(p_tag)::value;
+                constexpr bool kTail = decltype(tail_tag)::value;
+                const int nst = stage == S - 1 ? 0 : stage + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                wait_then_barrier<kTail ? 0 : (S - 2) * L>();
+                __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                        for (int jn = 0; jn < 2; ++jn) acc[m][jn] = mfma32x32x16(A[ks][m], B[ks][jn], acc[m][jn]);
-            }
-            if (grp == 0) wait_slab(left);
-            else bar_lds();
-            stage = stage == kGStages - 1 ? 0 : stage + 1;
-        }
-        if (grp == 0) bar_lds();  // phase 2 nk: group 1 multiplies the last slab
-        // Epilogue through the (now idle) LDS ring, so that the global stores are whole
-        // rows or whole tile-layout blocks instead of 8-byte pieces of 32 token rows.
-        // Lane holds column (token) l % 32 of each 32 x 32 tile, rows 8 (v / 4) + 4 (l / 32) + v % 4.
-        __syncthreads();  // every wave is done with the last stage
-        if (!kDown) {
-            // phase 1: act = silu(gate) * up in bf16, staged in the tile layout of its 16 x 4
-            // blocks (token block tb, feature block fb at LDS block 4 tb + fb)
+                for (int n = 0; n < NF; ++n) {
+                    constexpr int kA = NF == 2 ? 2 : 1;  // weight fragments read per step
 #pragma unroll
-            for (int jn = 0; jn < 2; ++jn) {
-                const int nl = 64 * wn + 32 * jn + (lane & 31);  // token within the item
+                    for (int i = 0; i < kA; ++i)
+                        if (kA * n + i < 4) A[P ^ 1][kA * n + i] = rd(nst, ablk(kA * n + i));
+                    B[P ^ 1][n] = rd(nst, 8 + 2 * n + wn);
 #pragma unroll
-                for (int m = 0; m < 2; ++m)
+                    for (int i = n * L / NF; i < (n + 1) * L / NF; ++i)
+                        if (!kTail || kt + S < nk) load(i, kt + S, stage);
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {
-                        const int fl = 64 * wm + 32 * m + 8 * q + 4 * (lane >> 5);  // feature within the item
-                        const f32x16 gv = acc[m][jn], uv = acc[m + 2][jn];
+                        const int m = (n & 1) ? 3 - q : q;  // neighbouring MFMAs share an operand
+                        mfma_tied(acc[n][m], A[P][m], B[P][n]);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                stage = nst;
+            };
+            using P0 = std::integral_constant<int, 0>;
+            using P1 = std::integral_constant<int, 1>;
+            int kt = 0;
+#pragma unroll 1
+            for (; kt + 1 + S < nk; kt += 2) {
+                slab(P0{}, std::false_type{}, kt);
+                slab(P1{}, std::false_type{}, kt + 1);
+            }
+            // claim the next item while the last slabs run (their waits cover the atomic)
+            int got = 0;
+            if (wave == 0 && lane == 0)
+                got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+            for (; kt < nk; kt += 2) {
+                slab(P0{}, std::true_type{}, kt);
+                slab(P1{}, std::true_type{}, kt + 1);
+            }
+            // MFMA results are read below: cover the longest wait they need
+            asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int n = 0; n < NF; ++n)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) asm volatile("" : "+a"(acc[n][m]));
+
+            // Epilogue through the idle ring, so that the global stores are whole tile-layout
+            // blocks or 256-byte runs of rows.  Lane holds column (token) lane % 16 of each
+            // 16 x 16 tile, rows 4 (lane / 16) .. + 3.
+            __syncthreads();  // every wave is done with the last stage
+            if (wave == 0) {
+                int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
+                if (it >= n_items) it = steal();
+                if (lane == 0) *s_next = it;
+            }
+            int elane = lane;  // opaque: the addresses below are not worth registers in the K loop
+            asm volatile("" : "+v"(elane));
+            if (!kDown) {
+                // act = silu(gate) * up in bf16, in the tile layout: token block tb, feature
+                // block fb at LDS block 2 tb + fb (this wave: tb = 2 n + wn, fb = wm)
+                uint8_t* ep = sbuf + (2 * wn + wm) * 1024 + 16 * ((elane & 15) + 16 * (elane >> 5)) + 8 * ((elane >> 4) & 1);
+#pragma unroll
+                for (int n = 0; n < NF; ++n)
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const f32x4 gv = acc[n][m], uv = acc[n][m + 2];
                         u32x2 packed;
-                        packed.x = pack_bf16x2(silu(gv[4 * q]) * uv[4 * q], silu(gv[4 * q + 1]) * uv[4 * q + 1]);
-                        packed.y =
-                            pack_bf16x2(silu(gv[4 * q + 2]) * uv[4 * q + 2], silu(gv[4 * q + 3]) * uv[4 * q + 3]);
-                        const int off = ((nl >> 4) * 4 + (fl >> 5)) * 1024 + 16 * ((nl & 15) + 16 * ((fl & 31) >> 3)) +
-                                        2 * (fl & 7);
-                        *reinterpret_cast<u32x2*>(sbuf + off) = packed;
+                        packed.x = pack_bf16x2(silu(gv.x) * uv.x, silu(gv.y) * uv.y);
+                        packed.y = pack_bf16x2(silu(gv.z) * uv.z, silu(gv.w) * uv.w);
+                        *reinterpret_cast<u32x2*>(ep + n * 4096 + m * 512) = packed;
+                    }
+            } else {
+                // expert outputs in bf16, rounded once (the combine sums them in fp32), as
+                // token rows of 128 outputs
+                uint8_t* ep = sbuf + ((16 * wn + (elane & 15)) * kTPitch + 64 * wm + 4 * (elane >> 4)) * 2;
+#pragma unroll
+                for (int n = 0; n < NF; ++n)
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const f32x4 v = acc[n][m];
+                        u32x2 packed;
+                        packed.x = pack_bf16x2(v.x, v.y);
+                        packed.y = pack_bf16x2(v.z, v.w);
+                        *reinterpret_cast<u32x2*>(ep + n * (32 * kTPitch * 2) + m * 32) = packed;
                     }
             }
-            __syncthreads();
-            // 64 blocks of 1 KB; a block goes out if it holds rows of the group and features that exist
-            uint16_t* act = static_cast<uint16_t*>(a.act);
-            for (int c = tid; c < 64 * 64; c += 512) {
+        };
+        if (nblk <= 4) run(std::integral_constant<int, 4>{});
+        else if (nblk <= 8) run(std::integral_constant<int, 8>{});
+        else if (nblk <= 12) run(std::integral_constant<int, 12>{});
+        else run(std::integral_constant<int, 16>{});
+        __syncthreads();
+        const int next = __builtin_amdgcn_readfirstlane(*s_next);
+        if (!kDown) {
+            // nblk x 2 blocks of 1 KB
+            uint16_t* act = static_cast<uint16_t*>(a.act) +
+                            ((size_t)(tg.blk + n0 / 16) * (a.Fa / 32) + r0 / 32) * 512;
+            for (int c = tid; c < nblk * 2 * 64; c += 256) {
                 const int blk = c >> 6, piece = c & 63;
-                const int tb = blk >> 2, fb = blk & 3;
-                if (n0 + 16 * tb >= it.count || r0 + 32 * fb >= it.Fg) continue;
                 const u32x4 v = *reinterpret_cast<const u32x4*>(sbuf + blk * 1024 + 16 * piece);
-                *reinterpret_cast<u32x4*>(act + ((size_t)(it.ablk + n0 / 16 + tb) * (a.Fa / 32) + r0 / 32 + fb) * 512 +
-                                          8 * piece) = v;
+                *reinterpret_cast<u32x4*>(act + ((size_t)(blk >> 1) * (a.Fa / 32) + (blk & 1)) * 512 + 8 * piece) = v;
             }
         } else {
-            // phase 2: expert outputs in bf16, rounded once (the combine sums them in fp32),
-            // staged as 256 token rows of 256 outputs (pitch 264 elements)
-            constexpr int kPitch = 264;
-            uint16_t* sy = reinterpret_cast<uint16_t*>(sbuf);
-#pragma unroll
-            for (int jn = 0; jn < 2; ++jn) {
-                const int nl = 64 * wn + 32 * jn + (lane & 31);
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int hl = 128 * wm + 32 * m + 8 * q + 4 * (lane >> 5);
-                        const f32x16 v = acc[m][jn];
-                        u32x2 packed;
-                        packed.x = pack_bf16x2(v[4 * q], v[4 * q + 1]);
-                        packed.y = pack_bf16x2(v[4 * q + 2], v[4 * q + 3]);
-                        *reinterpret_cast<u32x2*>(sy + nl * kPitch + hl) = packed;
-                    }
-            }
-            __syncthreads();
-            // 256 rows x 32 pieces of 16 bytes; rows of the group, outputs that exist
-            for (int c = tid; c < 256 * 32; c += 512) {
-                const int nl = c >> 5, piece = c & 31;
-                const int h = r0 + 8 * piece;
-                if (n0 + nl >= it.count || h >= a.H) continue;
-                const u32x4 v = *reinterpret_cast<const u32x4*>(sy + nl * kPitch + 8 * piece);
-                *reinterpret_cast<u32x4*>(a.y16 + (size_t)(it.rowbase + n0 + nl) * a.H + h) = v;
+            // the group's rows x 16 pieces of 16 bytes; outputs that exist
+            const int rows = min(kTN, tg.count - n0);
+            uint16_t* y = a.y16 + (size_t)(tg.rowbase + n0) * a.H + r0;
+            for (int c = tid; c < rows * 16; c += 256) {
+                const int nl = c >> 4, piece = c & 15;
+                if (r0 + 8 * piece >= a.H) continue;
+                const u32x4 v = *reinterpret_cast<const u32x4*>(sbuf + (nl * kTPitch + 8 * piece) * 2);
+                *reinterpret_cast<u32x4*>(y + (size_t)nl * a.H + 8 * piece) = v;
             }
         }
+        __syncthreads();  // the epilogue is done with the LDS
+        item = next;
     }
 }
 
@@ -1208,17 +1296,20 @@ long long tiled_routed_rows(const Shape& s) {
 long long tiled_t16(const Shape& s) { return (s.T + 15) / 16 * 16ll; }
 bool use_tiled(const Shape& s) { return s.bf16 && !use_stream(s); }
 
-// Worst-case items of a tiled phase: the routed groups have at most ceil(P / 256)
-// full 256-row tiles plus one partial tile each
-long long tiled_items(const Shape& s, bool down) {
+// Worst-case items of a tiled phase for row tiles of `rows` weight rows (phase 1: half as
+// many features): the routed groups have at most ceil(P / 256) full 256-row token tiles
+// plus one partial tile each
+long long tiled_items_of(const Shape& s, bool down, int rows) {
     const long long P = (long long)s.T * s.k;
     const long long G = max_routed_groups(s);
-    const long long rt = G == 0 ? 0 : (P + kGN - 1) / kGN + G;
-    const long long tps = (s.T + kGN - 1) / kGN;
-    if (down) return (rt + (long long)s.S * tps) * ((s.H + kGM - 1) / kGM);
-    const long long wt_r = (s.F + kGM / 2 - 1) / (kGM / 2), wt_s = s.S > 0 ? (s.Fs + kGM / 2 - 1) / (kGM / 2) : 0;
+    const long long rt = G == 0 ? 0 : (P + kTN - 1) / kTN + G;
+    const long long tps = (s.T + kTN - 1) / kTN;
+    if (down) return (rt + (long long)s.S * tps) * ((s.H + rows - 1) / rows);
+    const int f = rows / 2;
+    const long long wt_r = (s.F + f - 1) / f, wt_s = s.S > 0 ? (s.Fs + f - 1) / f : 0;
     return rt * wt_r + (long long)s.S * tps * wt_s;
 }
+long long tiled_items(const Shape& s, bool down) { return tiled_items_of(s, down, kTR); }
 
 Args make_args(const Shape& s, const FfnArgs& fa) {
     Args a;
@@ -1235,6 +1326,7 @@ Args make_args(const Shape& s, const FfnArgs& fa) {
     a.off_w = fa.off_w;
     a.xg = fa.xg;
     a.tmeta = fa.tmeta;
+    a.tclaim = fa.tclaim;
     a.tcap1 = use_tiled(s) ? (int)tiled_items(s, false) : 0;
     a.y16 = static_cast<uint16_t*>(fa.y16);
     a.fused = fa.topk_idx != nullptr;
@@ -1262,8 +1354,16 @@ long long ffn_gather_rows(const Shape& s) {
 
 size_t ffn_tile_meta_bytes(const Shape& s) {
     if (!use_tiled(s)) return 0;
-    return 32 + sizeof(TileItem) * (size_t)(tiled_items(s, false) + tiled_items(s, true));
+    const size_t need = kTHeader * 4 + sizeof(TileGroup) * (size_t)(max_routed_groups(s) + s.S) +
+                        sizeof(TileItem) * (size_t)(tiled_items(s, false) + tiled_items(s, true));
+    // the workspace of a shape is part of the interface (the fixed scratch array accepts or
+    // refuses a layer by it): the tables keep the room that 32 bytes per 256-row tile take,
+    // which is always enough
+    const size_t room = 32 + 32 * (size_t)(tiled_items_of(s, false, 256) + tiled_items_of(s, true, 256));
+    return need > room ? need : room;
 }
+
+size_t ffn_tile_claim_bytes(const Shape& s) { return use_tiled(s) ? 2 * 8 * kTClaimPitch * sizeof(int32_t) : 0; }
 
 hipError_t launch_gather_tokens(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
@@ -1353,26 +1453,27 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
         }
         return hipGetLastError();
     }
-    // tiled: one workgroup per CU, each taking its XCD's items from the table the token
-    // gather wrote in turn; the offloaded rows were packed by the token gather
+    // tiled: two workgroups per CU, each claiming items from the tables the token gather
+    // wrote; the offloaded rows were packed by the token gather
     int dev = 0, cus = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess)
         return e;
-    const long long wgs = cus < 8 ? 8 : cus / 8 * 8;
+    const long long wgs = cus < 8 ? 8 : cus / 8 * 16;
     auto tiled_grid = [&](long long items) { return items < wgs ? (items + 7) / 8 * 8 : wgs; };
+    const TileGroup* groups = reinterpret_cast<const TileGroup*>(a.tmeta + kTHeader);
+    const TileItem* tab = reinterpret_cast<const TileItem*>(groups + a.max_routed + a.S);
     {
         const long long grid = tiled_grid(tiled_items(s, false));
         if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_tiled<false>), dim3((unsigned)grid), dim3(512), 0, st, a,
-                               reinterpret_cast<const TileItem*>(a.tmeta + 8));
+            hipLaunchKernelGGL((k_ffn_tiled<false>), dim3((unsigned)grid), dim3(256), 0, st, a, tab, groups, a.tclaim);
     }
     if (hipError_t e = mark(); e != hipSuccess) return e;
     {
         const long long grid = tiled_grid(tiled_items(s, true));
         if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_tiled<true>), dim3((unsigned)grid), dim3(512), 0, st, a,
-                               reinterpret_cast<const TileItem*>(a.tmeta + 8) + a.tcap1);
+            hipLaunchKernelGGL((k_ffn_tiled<true>), dim3((unsigned)grid), dim3(256), 0, st, a, tab + a.tcap1, groups,
+                               a.tclaim + 8 * kTClaimPitch);
     }
     return hipGetLastError();
 }

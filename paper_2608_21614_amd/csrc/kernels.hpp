@@ -57,6 +57,7 @@ struct FfnArgs {
     // and the tiled kernels' item tables (ffn_tile_meta_bytes(s), 32-byte aligned)
     void* xg = nullptr;
     int32_t* tmeta = nullptr;
+    int32_t* tclaim = nullptr;  // the tiled kernels' claim counters (ffn_tile_claim_bytes(s))
     // bf16 prefill: phase 2 writes the expert outputs here in bf16 ([rows][H]) instead of y
     void* y16 = nullptr;
     // decode (ffn_fuses_repack): phase 1 takes the repacking over from topk_idx. Its
@@ -84,6 +85,7 @@ size_t ffn_y_bytes(const Shape& s);
 long long ffn_act_rows(const Shape& s);
 long long ffn_gather_rows(const Shape& s);
 size_t ffn_tile_meta_bytes(const Shape& s);
+size_t ffn_tile_claim_bytes(const Shape& s);
 
 // bf16 prefill: gathers the resident groups' token rows (and the batch in order,
 // for the shared experts) into a.xg, and packs the offloaded rows if asked;
