@@ -92,6 +92,10 @@ T* at(void* ws, size_t off) {
     return reinterpret_cast<T*>(static_cast<char*>(ws) + off);
 }
 
+// The tiled FFN's tables.  The fp32 ones (a few words a group) take the room of the scores,
+// which nothing reads once the routing is done: 4 T E bytes, T > 64, against 32 + 24 (E + S).
+int32_t* tile_meta(const Shape& s, const Layout& L, void* ws) { return at<int32_t>(ws, s.bf16 ? L.meta : L.logits); }
+
 moe_status hip_status(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_HIP; }
 
 constexpr int kMaxDevices = 64;
@@ -192,7 +196,7 @@ moe_status moe_grouped_ffn(const moe_dims* dims, const void* x, const int32_t* p
     a.w13 = w13; a.w2 = w2; a.ws13 = ws13; a.ws2 = ws2;
     a.act = at<char>(ws, L.act);
     a.xg = at<char>(ws, L.xg);
-    a.tmeta = at<int32_t>(ws, L.meta);
+    a.tmeta = tile_meta(s, L, ws);
     a.tclaim = at<int32_t>(ws, L.part);
     a.Fa = L.Fa;
     a.ks = L.ks;
@@ -202,7 +206,7 @@ moe_status moe_grouped_ffn(const moe_dims* dims, const void* x, const int32_t* p
     const bool y16 = saem::ffn_y_bf16(s);
     a.y = (L.ks == 1 && !y16) ? y : at<float>(ws, L.y);
     a.y16 = y16 ? at<char>(ws, L.y) : nullptr;
-    hipError_t e = saem::launch_gather_tokens(s, a, hs);
+    hipError_t e = saem::launch_ffn_prepare(s, a, hs);
     if (e == hipSuccess) e = saem::launch_grouped_ffn(s, a, hs);
     if (e == hipSuccess && (L.ks > 1 || y16))
         e = saem::launch_reduce_splits(s, counts, expert_slot, y16 ? a.y16 : a.y, y16, L.ks, a.y_ks_stride, y, hs);
@@ -283,14 +287,11 @@ static moe_status layer_forward(const moe_layer_args* a, void* ws, size_t ws_byt
         for (int i = 3; i < MOE_STAGE_EVENTS && e == hipSuccess; ++i) e = mark(hipSuccess, i);
         return hip_status(e);
     }
-    const bool fold_pack = saem::ffn_packs_offloaded(s);
     saem::FfnArgs f;
-    if (fold_pack) {
-        f.topk_w = w;
-        f.n_res = nres;
-        f.off_rows = a->off_rows;
-        f.off_w = a->off_w;
-    }
+    f.topk_w = w;
+    f.n_res = nres;
+    f.off_rows = a->off_rows;
+    f.off_w = a->off_w;
     f.x = a->x; f.perm = perm; f.counts = counts; f.seg_start = seg; f.expert_slot = a->expert_slot;
     if (fuse_repack) {
         f.topk_idx = idx;
@@ -303,7 +304,7 @@ static moe_status layer_forward(const moe_layer_args* a, void* ws, size_t ws_byt
     f.w13 = a->w13; f.w2 = a->w2; f.ws13 = a->ws13; f.ws2 = a->ws2;
     f.act = at<char>(ws, L.act);
     f.xg = at<char>(ws, L.xg);
-    f.tmeta = at<int32_t>(ws, L.meta);
+    f.tmeta = tile_meta(s, L, ws);
     f.tclaim = at<int32_t>(ws, L.part);
     f.Fa = L.Fa;
     const bool y16 = saem::ffn_y_bf16(s);
@@ -311,11 +312,9 @@ static moe_status layer_forward(const moe_layer_args* a, void* ws, size_t ws_byt
     f.y16 = y16 ? at<char>(ws, L.y) : nullptr;
     f.ks = L.ks;
     f.y_ks_stride = L.rows * (long long)s.H;
-    // the token gather of the bf16 prefill path (with the offloaded-row pack), or the
-    // standalone pack of the fp32 prefill path; at decode the pack is in FFN phase 2
-    if (e == hipSuccess)
-        e = mark(fold_pack ? saem::launch_gather_tokens(s, f, hs)
-                           : saem::launch_offload_pack(s, a->x, w, perm, nres, a->off_rows, a->off_w, hs), 3);
+    // prefill: the tiled FFN's tables, the bf16 token gather and the offloaded-row pack; at
+    // decode the pack is in FFN phase 2
+    if (e == hipSuccess) e = mark(saem::launch_ffn_prepare(s, f, hs), 3);
     if (e == hipSuccess) e = mark(saem::launch_grouped_ffn(s, f, hs, ev[4]), 5);
     if (e == hipSuccess)
         e = mark(saem::launch_combine(s, idx, w, inv, a->expert_slot, at<char>(ws, L.y), y16, L.ks, f.y_ks_stride,

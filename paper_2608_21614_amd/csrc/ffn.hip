@@ -12,9 +12,8 @@
 // MFMA A operands.
 //
 // Two kernel families:
-//  * stream  (T <= 64, decode, and fp32 prefill; bf16 MFMA 16x16x32, fp32 MFMA
-//    16x16x4): at decode the weights are streamed from HBM exactly once.  A
-//    workgroup owns 32 features (phase 1: 32 gate + 32 up weight rows) or 64
+//  * stream  (T <= 64, decode; bf16 MFMA 16x16x32, fp32 MFMA 16x16x4): the weights
+//    are streamed from HBM exactly once.  A workgroup owns 32 features (phase 1: 32 gate + 32 up weight rows) or 64
 //    outputs (phase 2: 64 rows of W2) of one expert; the weights are the MFMA
 //    M side and the expert's tokens the N side, in tiles of 16.  Its four waves
 //    split K interleaved -- wave w takes the 32-wide K steps w, w+4, w+8, ... --
@@ -26,21 +25,19 @@
 //    partial tiles are summed through LDS in wave order.  Phase 2 also splits K
 //    across workgroups into `ks` chunks whose partial sums the combine adds in
 //    fixed order.  SwiGLU is applied in the phase-1 epilogue, so the gate and up
-//    projections are never stored.  fp32 batches with T > 64 run this kernel on
-//    chunks of 64 rows of a group: an item is then (group, weight rows, chunk),
-//    found from a prefix over the active groups that every workgroup computes.
+//    projections are never stored.
 //    In the fused forward at decode, phase 1 also does the repacking: its
 //    workgroups count the top-k ids themselves (the batch is at most 512 pairs)
 //    and look their group's tokens up in them, one extra workgroup writes the
 //    repack's outputs for phase 2 and the combine, and phase 2's trailing
 //    workgroups pack the offloaded rows.  That saves the repack's launch and
 //    its chain of dependent memory round trips before the weights start to flow.
-//  * tiled   (bf16, T > 64, prefill): output tiles of 128 weight rows x up to 256 rows
-//    of a group (four waves on MFMA 16x16x32), two persistent workgroups per CU that
+//  * tiled   (T > 64, prefill; fp32 has a kernel of its own): output tiles of 128
+//    weight rows x up to 256 (fp32: 128) rows of a group (four waves on MFMA 16x16x32), two persistent workgroups per CU that
 //    claim items from a queue per XCD, both operands read as 1 KB tile-layout blocks by
-//    direct global->LDS loads through a ring of stages; a token gather first copies the
-//    resident groups' rows into that layout, and phase 1 writes the activations in it;
-//    the expert outputs are bf16.
+//    direct global->LDS loads through a ring of stages; for bf16 a token gather first
+//    copies the resident groups' rows into that layout, phase 1 writes the activations
+//    in it, and the expert outputs are bf16.
 // Both read counts and offsets from device memory: the stream kernel's grid is
 // sized for the worst case on the host and surplus workgroups exit at once; the
 // tiled kernel runs two workgroups per CU.
@@ -74,7 +71,6 @@ struct Args {
     int max_routed;   // routed groups the grid reserves (>= active resident experts)
     int ipg_r;        // items (workgroups) per routed group
     int ipg_s;        // items per shared group
-    int chunked;      // stream kernel: items cover the groups' rows in chunks of 64 (fp32 prefill)
     // offloaded-row pack done by the workgroups past the FFN items (phase 1; phase 2
     // in the fused path)
     const float* topk_w;
@@ -82,9 +78,9 @@ struct Args {
     void* off_rows;
     float* off_w;
     void* xg;         // bf16 prefill: gathered token rows in the tile layout
-    int32_t* tmeta;   // bf16 prefill: item tables of the tiled kernels
+    int32_t* tmeta;   // prefill: tables of the tiled kernels
     int tcap1;        // capacity of the phase-1 table
-    int32_t* tclaim;  // bf16 prefill: claim counters of the tiled kernels, eight per phase
+    int32_t* tclaim;  // prefill: claim counters of the tiled kernels, eight per phase
     uint16_t* y16;    // bf16 prefill: expert outputs [rows][H] in bf16 (instead of y)
     // decode with the repacking in phase 1 (fused): the ids, and the repack's outputs
     int fused;
@@ -344,7 +340,7 @@ __device__ int group_prefix(int n, int* s_out, int* s_tot, Fn f) {
 }
 
 // ---------------------------------------------------------------------------
-// stream kernel (decode, fp32 prefill)
+// stream kernel (decode)
 // ---------------------------------------------------------------------------
 
 // 16-row weight tiles per stream workgroup: two with a single token tile (twice
@@ -377,13 +373,11 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
     auto& s_red = *reinterpret_cast<f32x4 (*)[4][MT][NT][kWave]>(s_raw);
     __shared__ int s_scr[513];  // fused prologue: pairs and slot per expert, active experts
     __shared__ int s_gtok[64];  // fused prologue: the group's token rows
-    __shared__ int s_ipre[kGMaxGroups + 1];
-    __shared__ int s_tot;
     __shared__ int s_pos;  // slot-mapped items: the slot's place in the active list
 
     const int item = blockIdx.x;
     const int n_items = a.max_routed * a.ipg_r + a.S * a.ipg_s;
-    if (!a.chunked && item >= n_items) {
+    if (item >= n_items) {
         if (a.fused && !kDown) {  // the fused path's repack: one workgroup, P <= 512
             if (item == n_items)
                 repack_chunks<256>(a.T, a.E, a.k, a.slots, 0, (a.T * a.k + 255) / 256, a.topk_idx, a.expert_slot,
@@ -402,10 +396,10 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
     // item of the fused phase 1 when every slot can hold an active expert: item gi then
     // takes slot gi, whose weights are known at once, and issues its first weight batch
     // before the prologue finds the slot's expert, its rows and its tokens.
-    const bool shared_item = !a.chunked && item < a.S * a.ipg_s;
-    const bool by_slot = !a.chunked && a.fused && !kDown && a.slot_items && !shared_item;
+    const bool shared_item = item < a.S * a.ipg_s;
+    const bool by_slot = a.fused && !kDown && a.slot_items && !shared_item;
     Group g;
-    int sub = 0, n0 = 0;  // n0: first row of the group this item covers
+    int sub = 0;
     int slot = -1;
     if (shared_item) {
         g = shared_group(a, item / a.ipg_s, sizeof(Elt));
@@ -487,32 +481,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
     }
     // shared groups first: their items can be longer (Fs > F in phase 2), so they
     // start in the first wave of workgroups instead of forming a tail
-    if (a.chunked) {
-        // group gi (the S shared groups, then the active routed ones) owns
-        // ipg x ceil(rows / 16 NT) items, the chunks of one weight slice adjacent
-        constexpr int kRows = 16 * NT;
-        auto rows_of = [&](int gi) { return gi < a.S ? a.T : max(s_info[gi - a.S].y, 0); };
-        const int total = group_prefix(a.S + nact, s_ipre, &s_tot, [&](int gi) {
-            return (gi < a.S ? a.ipg_s : a.ipg_r) * ((rows_of(gi) + kRows - 1) / kRows);
-        });
-        if (item >= total) return;
-        int lo = 0, hi = a.S + nact - 1;  // last group with s_ipre[gi] <= item
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_ipre[mid] <= item) lo = mid;
-            else hi = mid - 1;
-        }
-        const int nch = (rows_of(lo) + kRows - 1) / kRows;
-        const int local = item - s_ipre[lo];
-        sub = local / nch;
-        n0 = (local % nch) * kRows;
-        if (lo < a.S) {
-            g = shared_group(a, lo, sizeof(Elt));
-        } else {
-            const int4 info = s_info[lo - a.S];
-            g = routed_group_of(a, info.x, info.y, info.z, sizeof(Elt));
-        }
-    } else if (by_slot) {
+    if (by_slot) {
         // the slot's place in the active list (the lowest, should two experts share a slot)
         for (int p = threadIdx.x; p < nact; p += 256)
             if (s_info[p].z == slot) atomicMin(&s_pos, p);
@@ -540,12 +509,12 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
     }
 
     // token operand rows (N side)
-    const int ntile = min(NT, (g.count - n0 + 15) / 16);
+    const int ntile = min(NT, (g.count + 15) / 16);
     const Elt* bp[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         bp[j] = nullptr;
-        const int n = n0 + 16 * j + r;
+        const int n = 16 * j + r;
         if (!kDown) {
             const int t = (a.fused && g.routed) ? (n < g.count ? s_gtok[n] : -1) : group_token(a, g, n);
             if (t >= 0) bp[j] = static_cast<const Elt*>(a.x) + (size_t)t * a.H + kq;
@@ -557,7 +526,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
     // the K loop for NL token tiles; in the bf16 kernels a group that fills one or two
     // 16-token tiles runs a copy with that many, without the MFMAs of the tiles past its end
     // (separate copies, not a branch in the loop, so that their accumulators never live at
-    // once).  The fp32 prefill kernel measured slower with a copy and keeps one loop.
+    // once).  fp32 keeps one loop.
     auto k_loop = [&](auto nl_tag) {
         constexpr int NL = decltype(nl_tag)::value;
         f32x4 acc[MT][NL];
@@ -590,7 +559,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
         {
             F8 B0[U][NL], B1[U][NL];
             if (nb > 0) load_x(B0, 0);
-            // (rolled: unrolling this loop, which the lambda otherwise invites, slows the fp32 kernel)
+            // (rolled: unrolling this loop, which the lambda otherwise invites, costs registers)
 #pragma unroll 1
             for (int b = 0; b < nb; b += 2) {
                 if (b + 1 < nb) load(A1, B1, b + 1);
@@ -634,7 +603,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
             const int m = task / (NT * kWave);
             const int j = (task / kWave) % NT;
             const int l = task % kWave;
-            const int n = n0 + 16 * j + (l & 15);
+            const int n = 16 * j + (l & 15);
             if (j >= ntile || n >= g.count) continue;
             f32x4 gv = s_red[0][m][j][l], uv = s_red[0][m + MH][j][l];
 #pragma unroll
@@ -659,7 +628,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
             const int m = task / (NT * kWave);
             const int j = (task / kWave) % NT;
             const int l = task % kWave;
-            const int n = n0 + 16 * j + (l & 15);
+            const int n = 16 * j + (l & 15);
             if (j >= ntile || n >= g.count) continue;
             f32x4 v = s_red[0][m][j][l];
 #pragma unroll
@@ -787,19 +756,13 @@ __host__ __device__ constexpr int weight_tiles(int H, int Fg, bool down) {
     return down ? (H + kTR - 1) / kTR : (Fg + kTF - 1) / kTF;
 }
 
-// Writes the item tables of both phases (workgroups part = 0 .. parts - 1 share the
-// entries; part 0 also writes the groups, the item counts and clears the claim counters).
-// The groups -- the S shared experts and the active resident routed ones, with their
-// (segment start, count, slot) in s_info and their row-block prefix in s_bpre -- are
-// taken in order of falling row count, so that the long items start first.  Inside a group
-// the items go through blocks of kTB token tiles, weight tile by weight tile: consecutive
-// items share their weight and token panels.
-__device__ void write_tile_items(const Args& a, int nact, const int4* s_info, const int* s_bpre, int rb_routed,
-                                 int* s_ipre, int* s_tot, int* s_rows, int16_t* s_ord, int part, int parts) {
+// The groups of the tiled kernels -- the S shared experts and the active resident routed
+// ones, with their (segment start, count, slot) in s_info -- in order of falling row count,
+// so that the long items start first: s_ord[o] = group, s_rows[group] = its rows (group gi:
+// shared expert gi for gi < S, else entry gi - S of the active list).
+__device__ void order_groups(const Args& a, int nact, const int4* s_info, int* s_rows, int16_t* s_ord) {
     const int ng = nact + a.S;
-    const int tb16 = (a.T + 15) / 16;
     const int P = a.T * a.k;
-    // group gi: shared expert gi for gi < S, else entry gi - S of the active list
     for (int gi = threadIdx.x; gi < ng; gi += 256) {
         int rows = a.T;
         if (gi >= a.S) {
@@ -819,26 +782,51 @@ __device__ void write_tile_items(const Args& a, int nact, const int4* s_info, co
         s_ord[rank] = (int16_t)gi;
     }
     __syncthreads();
-    TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);
-    if (part == 0) {
-        if (threadIdx.x < 2 * 8) a.tclaim[threadIdx.x * kTClaimPitch] = 0;
-        for (int o = threadIdx.x; o < ng; o += 256) {
-            const int gi = s_ord[o];
-            TileGroup g;
-            g.count = s_rows[gi];
-            if (gi < a.S) {
-                g.wsel = -(gi + 1);
-                g.rowbase = P + gi * a.T;
-                g.blk = rb_routed + gi * tb16;
-            } else {
-                const int4 inf = s_info[gi - a.S];
-                g.wsel = inf.z;
-                g.rowbase = min(max(inf.x, 0), P);
-                g.blk = s_bpre[gi - a.S];
-            }
-            groups[o] = g;
+}
+
+// Writes the ordered groups' table and clears the claim counters.  s_bpre: the routed
+// groups' row-block prefix (rb_routed blocks in all); without it (fp32) a group's
+// activations are its rows in the row space.
+__device__ void write_tile_groups(const Args& a, int ng, const int4* s_info, const int* s_rows, const int16_t* s_ord,
+                                  const int* s_bpre, int rb_routed, TileGroup* groups) {
+    const int P = a.T * a.k;
+    if (threadIdx.x < 2 * 8) a.tclaim[threadIdx.x * kTClaimPitch] = 0;
+    for (int o = threadIdx.x; o < ng; o += 256) {
+        const int gi = s_ord[o];
+        TileGroup g;
+        g.count = s_rows[gi];
+        if (gi < a.S) {
+            g.wsel = -(gi + 1);
+            g.rowbase = P + gi * a.T;
+            g.blk = rb_routed + gi * ((a.T + 15) / 16);
+        } else {
+            const int4 inf = s_info[gi - a.S];
+            g.wsel = inf.z;
+            g.rowbase = min(max(inf.x, 0), P);
+            g.blk = s_bpre ? s_bpre[gi - a.S] : 0;
         }
+        groups[o] = g;
     }
+}
+
+// Item `local` of a group with nwt weight tiles and ntt token tiles: the items go through
+// blocks of kTB token tiles, weight tile by weight tile, so that consecutive items share
+// their weight and token panels.
+__device__ __forceinline__ void item_tiles(int local, int nwt, int ntt, int* wt, int* tt) {
+    const int tb = local / (nwt * kTB), rest = local - tb * nwt * kTB;
+    const int width = min(kTB, ntt - tb * kTB);
+    *wt = rest / width;
+    *tt = tb * kTB + rest % width;
+}
+
+// Writes the item tables of both bf16 phases (workgroups part = 0 .. parts - 1 share the
+// entries; part 0 also writes the groups and the item counts).
+__device__ void write_tile_items(const Args& a, int nact, const int4* s_info, const int* s_bpre, int rb_routed,
+                                 int* s_ipre, int* s_tot, int* s_rows, int16_t* s_ord, int part, int parts) {
+    const int ng = nact + a.S;
+    order_groups(a, nact, s_info, s_rows, s_ord);
+    TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);
+    if (part == 0) write_tile_groups(a, ng, s_info, s_rows, s_ord, s_bpre, rb_routed, groups);
     TileItem* tab = reinterpret_cast<TileItem*>(groups + a.max_routed + a.S);
     for (int ph = 0; ph < 2; ++ph) {
         const bool down = ph == 1;
@@ -858,11 +846,11 @@ __device__ void write_tile_items(const Args& a, int nact, const int4* s_info, co
             const int nwt = weight_tiles(a.H, gi < a.S ? a.Fs : a.F, down);
             const int ntt = (s_rows[gi] + kTN - 1) / kTN;
             const int local = i - s_ipre[lo];
-            const int tb = local / (nwt * kTB), rest = local - tb * nwt * kTB;
-            const int width = min(kTB, ntt - tb * kTB);
+            int wt, tt;
+            item_tiles(local, nwt, ntt, &wt, &tt);
             TileItem it;
-            it.wt = rest / width;
-            it.gt = (uint32_t)lo | (uint32_t)(tb * kTB + rest % width) << 9;
+            it.wt = wt;
+            it.gt = (uint32_t)lo | (uint32_t)tt << 9;
             out[i] = it;
         }
         if (part == 0 && threadIdx.x == 0) a.tmeta[ph] = total;
@@ -951,6 +939,24 @@ __device__ __forceinline__ int claimed_item(int q, int x) {
     return ((q / kTChunk) * 8 + x) * kTChunk + q % kTChunk;
 }
 
+// The next item of XCD queue *xcd, or of another queue (then *xcd) once that one is empty;
+// -1 when all are.  By one wave; the counters only grow, so the loop ends.
+__device__ int next_item(int32_t* claim, int q0, int n_items, int* xcd) {
+    const int lane = lane_id();
+    for (;;) {
+        const int x = (*xcd + (lane & 7)) & 7;
+        const int q = __hip_atomic_load(claim + x * kTClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const unsigned long long some = __ballot(lane < 8 && claimed_item(q0 + q, x) < n_items);
+        if (!some) return -1;
+        *xcd = (*xcd + __ffsll((long long)some) - 1) & 7;
+        int got = 0;
+        if (lane == 0)
+            got = __hip_atomic_fetch_add(claim + *xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), *xcd);
+        if (it < n_items) return it;
+    }
+}
+
 // A persistent kernel, two workgroups per CU.  tab, groups: this phase's tables, passed on
 // their own and restrict-qualified, so that the compiler knows the kernel's stores leave
 // them alone and reads them through scalar loads.  claim: eight counters, one per XCD.
@@ -970,25 +976,9 @@ __global__ void __launch_bounds__(256, 2)
     int xcd = blockIdx.x % 8;
     int item = claimed_item(blockIdx.x / 8, xcd);
 
-    // the next item of XCD queue xcd, or of another queue once that one is empty; -1 when all
-    // are.  By wave 0; the counters only grow, so the loop ends.
-    auto steal = [&]() -> int {
-        for (;;) {
-            const int x = (xcd + (lane & 7)) & 7;
-            const int q = __hip_atomic_load(claim + x * kTClaimPitch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const unsigned long long some = __ballot(lane < 8 && claimed_item(q0 + q, x) < n_items);
-            if (!some) return -1;
-            xcd = (xcd + __ffsll((long long)some) - 1) & 7;
-            int got = 0;
-            if (lane == 0)
-                got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
-            if (it < n_items) return it;
-        }
-    };
     if (item >= n_items) {
         if (wave == 0) {
-            const int it = steal();
+            const int it = next_item(claim, q0, n_items, &xcd);
             if (lane == 0) *s_next = it;
         }
         __syncthreads();
@@ -1141,7 +1131,7 @@ __global__ void __launch_bounds__(256, 2)
             __syncthreads();  // every wave is done with the last stage
             if (wave == 0) {
                 int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
-                if (it >= n_items) it = steal();
+                if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
                 if (lane == 0) *s_next = it;
             }
             int elane = lane;  // opaque: the addresses below are not worth registers in the K loop
@@ -1204,6 +1194,280 @@ __global__ void __launch_bounds__(256, 2)
         }
         __syncthreads();  // the epilogue is done with the LDS
         item = next;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// tiled kernel, fp32 prefill
+// ---------------------------------------------------------------------------
+//
+// The same items (128 weight rows x up to 128 of a group's rows) and claim queues on
+// v_mfma_f32_16x16x4_f32.  fp32 has a sixteenth of the bf16 MFMA rate, so the MFMAs bound
+// it and its operands need no gathered copy: a 32-wide K slab of a row-major token row is a
+// whole 128-byte line, loaded straight into the LDS (eight lanes a row).  LDS images, both
+// read without bank conflicts:
+//   weight block (2 KB): two 1 KB chunks of 32 lanes' values, in each the lanes' first 16
+//     bytes and then their second ones;
+//   token block (16 rows x 128 bytes): row r's 16-byte piece p at slot p ^ (r % 8).
+// Two stages or more per ring; a slab's fragments are read behind its barrier, while the
+// CU's other workgroup multiplies.  The accumulators are added into a second set every
+// kFFlush slabs, so that no fp32 sum chain is longer than 256 products (the interleaved K
+// split of the stream kernel, which ran these batches before, had chains of K / 4).
+//
+// Before (the decode stream kernel over 64-row chunks: 64 x 64 tiles, both operands from L2
+// into registers, which asks 16 bytes per clock of every CU's load path) and now, phase 1 /
+// phase 2 in us:
+//   64 experts x 256 rows, H 2048, F 1408:  1907 / 1014 -> 1567 / 787 (121 TFLOP/s)
+//   48 experts x 100 rows, H 2048, F 1408:   713 /  388 ->  647 / 283
+//   48 experts x  40 rows, H 2048, F 1408:   395 /  218 ->  350 / 157
+//    8 experts x  83 rows, H 4096, F 4096:   801 /  412 ->  402 / 222
+// Token tiles of 64 or 96 rows instead of 128: 1693 / 871 and 1674 / 857 at 256 rows.  What is
+// left: the last round of items (2816 for 512 workgroups in the first line) and the fragment
+// reads behind each barrier.
+
+constexpr int kFN = 128;    // group rows per item
+constexpr int kFLds = 72 * 1024;  // the ring of a workgroup: two workgroups per CU
+constexpr int kFFlush = 8;  // slabs between two additions into the second accumulators
+
+__device__ __forceinline__ void mfma_tied_f32(f32x4& acc, float a, float b) {
+    asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+
+// 16 bytes per lane from a per-lane address (see the uniform-base form above).
+__device__ __forceinline__ void lds_load_1k_lanes(uint32_t lds, const void* p) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+                 :
+                 : "s"(lds), "v"(p)
+                 : "memory", "m0");
+}
+
+// fp32 prefill: the groups in order and the prefix of their items, in tmeta: int32 header[8]
+// (items of phase 1, of phase 2, groups), TileGroup[groups], first item[groups] of phase 1
+// and of phase 2.  One workgroup; the others pack the offloaded rows.
+__global__ void __launch_bounds__(256) k_tile_groups(Args a) {
+    __shared__ int s_list[256];
+    __shared__ int4 s_info[256];
+    __shared__ int s_wsum[8];
+    __shared__ int s_ipre[kGMaxGroups + 1];
+    __shared__ int s_rows[kGMaxGroups];
+    __shared__ int16_t s_ord[kGMaxGroups];
+    if (blockIdx.x > 0) {
+        pack_offloaded(a, blockIdx.x - 1, gridDim.x - 1, 4);
+        return;
+    }
+    const int nact = list_active(a, s_list, s_wsum, s_info);
+    const int ng = nact + a.S;
+    order_groups(a, nact, s_info, s_rows, s_ord);
+    TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);
+    write_tile_groups(a, ng, s_info, s_rows, s_ord, nullptr, 0, groups);
+    int32_t* pre = reinterpret_cast<int32_t*>(groups + a.max_routed + a.S);
+    for (int ph = 0; ph < 2; ++ph) {
+        const int total = group_prefix(ng, s_ipre, s_wsum + 5 + ph, [&](int o) {
+            const int gi = s_ord[o];
+            return weight_tiles(a.H, gi < a.S ? a.Fs : a.F, ph == 1) * ((s_rows[gi] + kFN - 1) / kFN);
+        });
+        for (int o = threadIdx.x; o < ng; o += 256) pre[ph * (a.max_routed + a.S) + o] = s_ipre[o];
+        if (threadIdx.x == 0) a.tmeta[ph] = total;
+        __syncthreads();  // s_ipre is rewritten for the next phase
+    }
+    if (threadIdx.x == 0) a.tmeta[2] = ng;
+}
+
+template <bool kDown>
+__global__ void __launch_bounds__(256, 2)
+    k_ffn_tiled_f32(Args a, const TileGroup* __restrict__ groups, const int32_t* __restrict__ pre, int32_t* claim) {
+    __shared__ __attribute__((aligned(1024))) uint8_t sbuf[kFLds];
+    __shared__ int32_t s_next;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave & 1, wn = wave >> 1;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)sbuf;
+    const uint32_t woff = 16 * (2 * (lane & 31) + (lane >> 5));  // a lane's bytes of a 1 KB weight chunk
+    const int n_items = a.tmeta[kDown ? 1 : 0], ng = a.tmeta[2];
+    const int q0 = gridDim.x / 8;
+    int xcd = blockIdx.x % 8;
+    int item = claimed_item(blockIdx.x / 8, xcd);
+    if (item >= n_items) {
+        if (wave == 0) {
+            const int it = next_item(claim, q0, n_items, &xcd);
+            if (lane == 0) s_next = it;
+        }
+        __syncthreads();
+        item = __builtin_amdgcn_readfirstlane(s_next);
+    }
+
+    while (item >= 0) {
+        // last group whose first item is <= item: the groups at or below it, counted
+        int below = 0;
+        for (int o = 0; o < ng; o += kWave) below += __popcll(__ballot(o + lane < ng && pre[min(o + lane, ng - 1)] <= item));
+        const int go = __builtin_amdgcn_readfirstlane(below - 1);
+        const TileGroup tg = groups[go];
+        const bool shared = tg.wsel < 0;
+        const int Fg = shared ? a.Fs : a.F;
+        const int ntt = (tg.count + kFN - 1) / kFN;
+        int wt, tt;
+        item_tiles(item - pre[go], weight_tiles(a.H, Fg, kDown), ntt, &wt, &tt);
+        const int n0 = __builtin_amdgcn_readfirstlane(tt) * kFN;
+        const int r0 = __builtin_amdgcn_readfirstlane(wt) * (kDown ? kTR : kTF);
+        const int K = kDown ? Fg : a.H;
+        const int nk = K / 32;
+        const size_t wsize = (size_t)(kDown ? 1 : 2) * Fg * a.H;
+        const float* wbase = shared ? static_cast<const float*>(kDown ? a.ws2 : a.ws13) + (size_t)(-tg.wsel - 1) * wsize
+                                    : static_cast<const float*>(kDown ? a.w2 : a.w13) + (size_t)tg.wsel * wsize;
+        // this wave loads LDS weight blocks 2 wave, 2 wave + 1; phase 1: gate rows in blocks
+        // 0..3, up rows in 4..7; a row tile past the matrix reads tile 0 (never stored)
+        const float* gw[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int b = 2 * wave + i;
+            int rt;
+            if (kDown) {
+                rt = r0 / 16 + b;
+                if (16 * rt >= a.H) rt = 0;
+            } else {
+                rt = (b >> 2) * (Fg / 16) + r0 / 16 + (b & 3);
+            }
+            gw[i] = wbase + (size_t)rt * nk * 512;
+        }
+        const int rows = min(kFN, tg.count - n0);
+
+        // the item with its tokens in NB blocks (2, 4, 6 or 8)
+        auto run = [&](auto nb_tag) {
+            constexpr int NB = decltype(nb_tag)::value;
+            constexpr int NF = NB / 2;            // token fragments of a wave: blocks 2 n + wn
+            constexpr int LX = NB / 2, L = 4 + LX;  // loads of a wave per slab
+            constexpr int kSlab = (8 + NB) * 2048;
+            constexpr int S = NB <= 4 ? 3 : 2;    // stages of the ring
+            static_assert(S * kSlab <= kFLds, "ring");
+            // token row of this lane in load i: row 8 (j % 2) + lane / 8 of token block j / 2,
+            // j = wave LX + i; rows past the group read the item's first row (never stored)
+            const float* gx[LX];
+#pragma unroll
+            for (int i = 0; i < LX; ++i) {
+                const int n = 8 * (wave * LX + i) + (lane >> 3);
+                const int nn = n0 + (n < rows ? n : 0);
+                size_t row;
+                if (kDown) {
+                    row = (size_t)(tg.rowbase + nn) * a.Fa;
+                } else {
+                    int t = nn;
+                    if (!shared) {
+                        const int q = a.perm[tg.rowbase + nn];
+                        t = q >= 0 ? q / a.k : 0;
+                        t = t < a.T ? t : 0;
+                    }
+                    row = (size_t)t * a.H;
+                }
+                gx[i] = static_cast<const float*>(kDown ? a.act : a.x) + row + 4 * ((lane & 7) ^ (lane >> 3));
+            }
+            auto issue = [&](int kt, int stage) {
+                const uint32_t to = lds0 + stage * kSlab;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    lds_load_1k<false>(to + (2 * wave + i / 2) * 2048 + (i % 2) * 1024,
+                                       gw[i / 2] + (size_t)kt * 512 + (i % 2) * 256, woff);
+#pragma unroll
+                for (int i = 0; i < LX; ++i)
+                    lds_load_1k_lanes(to + 16384 + (wave * LX + i) * 1024, gx[i] + (size_t)kt * 32);
+            };
+            f32x4 acc[NF][4], tot[NF][4];
+#pragma unroll
+            for (int n = 0; n < NF; ++n)
+#pragma unroll
+                for (int m = 0; m < 4; ++m) acc[n][m] = tot[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int st = 0; st < S - 1; ++st)
+                if (st < nk) issue(st, st);
+            // this lane's first piece of a weight block, and of a token block's row lane % 16
+            const uint8_t* aw = sbuf + (lane >> 5) * 1024 + (lane & 31) * 16;
+            const uint8_t* bx = sbuf + 16384 + (lane & 15) * 128;
+            const int p0 = 2 * (lane >> 4), sw = lane & 7;
+            const int b_lo = ((p0 ^ sw) * 16), b_hi = (((p0 + 1) ^ sw) * 16);
+            int stage = 0, got = 0;
+#pragma unroll 1
+            for (int kt = 0; kt < nk; ++kt) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (S > 2 && nk - 1 - kt >= S - 2) wait_then_barrier<(S - 2) * L>();
+                else wait_then_barrier<0>();
+                __builtin_amdgcn_sched_barrier(0);
+                if (kt + S - 1 < nk) issue(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
+                // claim the next item while the last slabs run
+                if (kt == nk - 2 && wave == 0 && lane == 0)
+                    got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const int so = stage * kSlab;
+                f32x4 A[2][4], B[2][NF];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int m = 0; m < 4; ++m) {
+                        const int blk = kDown ? 4 * wm + m : (m < 2 ? 2 * wm + m : 4 + 2 * wm + m - 2);
+                        A[h][m] = *reinterpret_cast<const f32x4*>(aw + so + blk * 2048 + h * 512);
+                    }
+#pragma unroll
+                    for (int n = 0; n < NF; ++n)
+                        B[h][n] = *reinterpret_cast<const f32x4*>(bx + so + (2 * n + wn) * 2048 + (h ? b_hi : b_lo));
+                }
+                // K 8 (lane / 16) + 4 h + i of the slab, over all tiles before the next i
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int n = 0; n < NF; ++n)
+#pragma unroll
+                            for (int m = 0; m < 4; ++m) mfma_tied_f32(acc[n][m], A[h][m][i], B[h][n][i]);
+                if (kt % kFFlush == kFFlush - 1 || kt == nk - 1) {
+                    // the MFMAs' results are read as ordinary registers: cover their latency
+                    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int n = 0; n < NF; ++n)
+#pragma unroll
+                        for (int m = 0; m < 4; ++m) {
+                            asm volatile("" : "+v"(acc[n][m]));
+                            tot[n][m] += acc[n][m];
+                            acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        }
+                    asm volatile("s_nop 7" ::: "memory");
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                stage = stage == S - 1 ? 0 : stage + 1;
+            }
+            if (wave == 0) {
+                int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
+                if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
+                if (lane == 0) s_next = it;
+            }
+            // lane holds token lane % 16 of each 16 x 16 tile, weight rows 4 (lane / 16) .. + 3
+#pragma unroll
+            for (int n = 0; n < NF; ++n) {
+                const int nl = 16 * (2 * n + wn) + (lane & 15);
+                if (nl >= rows) continue;
+                if (!kDown) {
+                    float* dst = static_cast<float*>(a.act) + (size_t)(tg.rowbase + n0 + nl) * a.Fa + r0 + 32 * wm +
+                                 4 * (lane >> 4);
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const f32x4 gv = tot[n][m], uv = tot[n][m + 2];
+                        *reinterpret_cast<f32x4*>(dst + 16 * m) = f32x4{silu(gv.x) * uv.x, silu(gv.y) * uv.y,
+                                                                       silu(gv.z) * uv.z, silu(gv.w) * uv.w};
+                    }
+                } else {
+                    const int h = r0 + 64 * wm + 4 * (lane >> 4);
+                    float* dst = a.y + (size_t)(tg.rowbase + n0 + nl) * a.H + h;
+#pragma unroll
+                    for (int m = 0; m < 4; ++m)
+                        if (h + 16 * m < a.H) *reinterpret_cast<f32x4*>(dst + 16 * m) = tot[n][m];
+                }
+            }
+        };
+        const int nb = (rows + 31) / 32;
+        if (nb <= 1) run(std::integral_constant<int, 2>{});
+        else if (nb == 2) run(std::integral_constant<int, 4>{});
+        else if (nb == 3) run(std::integral_constant<int, 6>{});
+        else run(std::integral_constant<int, 8>{});
+        __syncthreads();  // every wave is done with the ring
+        item = __builtin_amdgcn_readfirstlane(s_next);
     }
 }
 
@@ -1283,8 +1547,6 @@ bool stream_weights(const Shape& s) {
 
 }  // namespace
 
-bool ffn_packs_offloaded(const Shape& s) { return use_stream(s) || s.bf16; }
-
 bool ffn_fuses_repack(const Shape& s) { return use_stream(s) && s.T > 0; }
 
 namespace {
@@ -1294,16 +1556,18 @@ long long tiled_routed_rows(const Shape& s) {
     return (long long)s.T * s.k + 15ll * max_routed_groups(s);
 }
 long long tiled_t16(const Shape& s) { return (s.T + 15) / 16 * 16ll; }
-bool use_tiled(const Shape& s) { return s.bf16 && !use_stream(s); }
+bool use_tiled(const Shape& s) { return !use_stream(s); }
+bool tiled_bf16(const Shape& s) { return s.bf16 && use_tiled(s); }
 
 // Worst-case items of a tiled phase for row tiles of `rows` weight rows (phase 1: half as
-// many features): the routed groups have at most ceil(P / 256) full 256-row token tiles
+// many features): the routed groups have at most ceil(P / tn) full token tiles of tn rows
 // plus one partial tile each
 long long tiled_items_of(const Shape& s, bool down, int rows) {
+    const int tn = s.bf16 ? kTN : kFN;
     const long long P = (long long)s.T * s.k;
     const long long G = max_routed_groups(s);
-    const long long rt = G == 0 ? 0 : (P + kTN - 1) / kTN + G;
-    const long long tps = (s.T + kTN - 1) / kTN;
+    const long long rt = G == 0 ? 0 : (P + tn - 1) / tn + G;
+    const long long tps = (s.T + tn - 1) / tn;
     if (down) return (rt + (long long)s.S * tps) * ((s.H + rows - 1) / rows);
     const int f = rows / 2;
     const long long wt_r = (s.F + f - 1) / f, wt_s = s.S > 0 ? (s.Fs + f - 1) / f : 0;
@@ -1319,7 +1583,6 @@ Args make_args(const Shape& s, const FfnArgs& fa) {
     a.act = fa.act; a.Fa = fa.Fa; a.y = fa.y; a.ks = fa.ks; a.y_ks_stride = fa.y_ks_stride;
     a.max_routed = max_routed_groups(s);
     a.ipg_r = a.ipg_s = 0;
-    a.chunked = 0;
     a.topk_w = fa.topk_w;
     a.n_res = fa.n_res;
     a.off_rows = fa.off_rows;
@@ -1327,7 +1590,7 @@ Args make_args(const Shape& s, const FfnArgs& fa) {
     a.xg = fa.xg;
     a.tmeta = fa.tmeta;
     a.tclaim = fa.tclaim;
-    a.tcap1 = use_tiled(s) ? (int)tiled_items(s, false) : 0;
+    a.tcap1 = tiled_bf16(s) ? (int)tiled_items(s, false) : 0;
     a.y16 = static_cast<uint16_t*>(fa.y16);
     a.fused = fa.topk_idx != nullptr;
     // every slot can hold an active expert: the fused phase 1 maps routed items to slots
@@ -1343,17 +1606,17 @@ Args make_args(const Shape& s, const FfnArgs& fa) {
 }  // namespace
 
 long long ffn_act_rows(const Shape& s) {
-    if (use_tiled(s)) return tiled_routed_rows(s) + (long long)s.S * tiled_t16(s);
+    if (tiled_bf16(s)) return tiled_routed_rows(s) + (long long)s.S * tiled_t16(s);
     return (long long)s.T * s.k + (long long)s.S * s.T;
 }
 
 long long ffn_gather_rows(const Shape& s) {
-    if (!use_tiled(s)) return 0;
+    if (!tiled_bf16(s)) return 0;
     return tiled_routed_rows(s) + (s.S > 0 ? tiled_t16(s) : 0);
 }
 
 size_t ffn_tile_meta_bytes(const Shape& s) {
-    if (!use_tiled(s)) return 0;
+    if (!tiled_bf16(s)) return 0;
     const size_t need = kTHeader * 4 + sizeof(TileGroup) * (size_t)(max_routed_groups(s) + s.S) +
                         sizeof(TileItem) * (size_t)(tiled_items(s, false) + tiled_items(s, true));
     // the workspace of a shape is part of the interface (the fixed scratch array accepts or
@@ -1365,12 +1628,16 @@ size_t ffn_tile_meta_bytes(const Shape& s) {
 
 size_t ffn_tile_claim_bytes(const Shape& s) { return use_tiled(s) ? 2 * 8 * kTClaimPitch * sizeof(int32_t) : 0; }
 
-hipError_t launch_gather_tokens(const Shape& s, const FfnArgs& fa, hipStream_t st) {
+hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
     const Args a = make_args(s, fa);
-    const long long blocks = ffn_gather_rows(s) / 16;
     const int P = s.T * s.k;
     const int n_pack = (fa.off_rows || fa.off_w) ? (P < 256 ? P : 256) : 0;
+    if (!s.bf16) {
+        hipLaunchKernelGGL(k_tile_groups, dim3((unsigned)(1 + n_pack)), dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
+    const long long blocks = ffn_gather_rows(s) / 16;
     hipLaunchKernelGGL(k_gather_tokens, dim3((unsigned)(blocks + n_pack)), dim3(256), 0, st, a, (int)blocks);
     return hipGetLastError();
 }
@@ -1407,25 +1674,6 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
         return e;
     };
     Args a = make_args(s, fa);
-    if (!s.bf16 && !use_stream(s)) {
-        // fp32 prefill: the stream kernel over chunks of 64 rows; a workgroup per
-        // worst-case item: the routed groups hold at most ceil(P / 64) full chunks
-        // plus one partial chunk each
-        a.chunked = 1;
-        const long long chunks_r = a.max_routed == 0 ? 0 : ((long long)s.T * s.k + 63) / 64 + a.max_routed;
-        const long long chunks_s = (long long)s.S * ((s.T + 63) / 64);
-        a.ipg_r = s.F / 32;
-        a.ipg_s = s.S > 0 ? s.Fs / 32 : 1;
-        long long grid = a.ipg_r * chunks_r + a.ipg_s * chunks_s;
-        if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_stream<float, 4, false, false>), dim3((unsigned)grid), dim3(256), 0, st, a);
-        if (hipError_t e = mark(); e != hipSuccess) return e;
-        a.ipg_r = a.ipg_s = s.H / 64;
-        grid = a.ipg_r * (chunks_r + chunks_s);
-        if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_stream<float, 4, true, false>), dim3((unsigned)grid), dim3(256), 0, st, a);
-        return hipGetLastError();
-    }
     if (use_stream(s)) {
         const int nt = (s.T + 15) / 16;
         const bool sw = stream_weights(s);
@@ -1453,27 +1701,31 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
         }
         return hipGetLastError();
     }
-    // tiled: two workgroups per CU, each claiming items from the tables the token gather
-    // wrote; the offloaded rows were packed by the token gather
+    // tiled: two workgroups per CU, each claiming items from the tables written before; the
+    // offloaded rows were packed there
     int dev = 0, cus = 0;
     if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
     if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess)
         return e;
     const long long wgs = cus < 8 ? 8 : cus / 8 * 16;
-    auto tiled_grid = [&](long long items) { return items < wgs ? (items + 7) / 8 * 8 : wgs; };
     const TileGroup* groups = reinterpret_cast<const TileGroup*>(a.tmeta + kTHeader);
-    const TileItem* tab = reinterpret_cast<const TileItem*>(groups + a.max_routed + a.S);
-    {
-        const long long grid = tiled_grid(tiled_items(s, false));
-        if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_tiled<false>), dim3((unsigned)grid), dim3(256), 0, st, a, tab, groups, a.tclaim);
-    }
-    if (hipError_t e = mark(); e != hipSuccess) return e;
-    {
-        const long long grid = tiled_grid(tiled_items(s, true));
-        if (grid > 0)
-            hipLaunchKernelGGL((k_ffn_tiled<true>), dim3((unsigned)grid), dim3(256), 0, st, a, tab + a.tcap1, groups,
-                               a.tclaim + 8 * kTClaimPitch);
+    const long long n_groups = a.max_routed + a.S;
+    for (int down = 0; down < 2; ++down) {
+        const long long items = tiled_items(s, down == 1);
+        const unsigned grid = (unsigned)(items < wgs ? (items + 7) / 8 * 8 : wgs);
+        int32_t* claim = a.tclaim + down * 8 * kTClaimPitch;
+        if (grid > 0 && s.bf16) {
+            const TileItem* tab = reinterpret_cast<const TileItem*>(groups + n_groups) + (down ? a.tcap1 : 0);
+            if (down) hipLaunchKernelGGL((k_ffn_tiled<true>), dim3(grid), dim3(256), 0, st, a, tab, groups, claim);
+            else hipLaunchKernelGGL((k_ffn_tiled<false>), dim3(grid), dim3(256), 0, st, a, tab, groups, claim);
+        } else if (grid > 0) {
+            const int32_t* pre = reinterpret_cast<const int32_t*>(groups + n_groups) + down * n_groups;
+            if (down) hipLaunchKernelGGL((k_ffn_tiled_f32<true>), dim3(grid), dim3(256), 0, st, a, groups, pre, claim);
+            else hipLaunchKernelGGL((k_ffn_tiled_f32<false>), dim3(grid), dim3(256), 0, st, a, groups, pre, claim);
+        }
+        if (!down) {
+            if (hipError_t e = mark(); e != hipSuccess) return e;
+        }
     }
     return hipGetLastError();
 }
@@ -1491,7 +1743,7 @@ hipError_t launch_reduce_splits(const Shape& s, const int32_t* counts, const int
     return hipGetLastError();
 }
 
-bool ffn_y_bf16(const Shape& s) { return use_tiled(s); }
+bool ffn_y_bf16(const Shape& s) { return tiled_bf16(s); }
 
 size_t ffn_y_bytes(const Shape& s) {
     const long long rows = (long long)s.T * s.k + (long long)s.S * s.T;

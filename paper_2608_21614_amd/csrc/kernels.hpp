@@ -47,15 +47,16 @@ struct FfnArgs {
     float* y;           // [ks][rows][H] fp32 partial sums over K chunks of the down projection
     int ks;             // number of K chunks of the down projection
     long long y_ks_stride;
-    // optional: pack the offloaded rows in extra workgroups (of phase 1 at decode,
-    // of the token gather at bf16 prefill)
+    // optional: pack the offloaded rows in extra workgroups (of phase 2 in the fused decode
+    // path, of launch_ffn_prepare at prefill)
     const float* topk_w = nullptr;
     const int32_t* n_res = nullptr;
     void* off_rows = nullptr;
     float* off_w = nullptr;
-    // bf16 prefill: the token rows gathered into the MFMA tile layout, ffn_gather_rows(s) x H,
-    // and the tiled kernels' item tables (ffn_tile_meta_bytes(s), 32-byte aligned)
+    // bf16 prefill: the token rows gathered into the MFMA tile layout, ffn_gather_rows(s) x H
     void* xg = nullptr;
+    // prefill: the tiled kernels' tables (bf16: ffn_tile_meta_bytes(s); fp32: 32 + 24 bytes a
+    // group), 32-byte aligned, and
     int32_t* tmeta = nullptr;
     int32_t* tclaim = nullptr;  // the tiled kernels' claim counters (ffn_tile_claim_bytes(s))
     // bf16 prefill: phase 2 writes the expert outputs here in bf16 ([rows][H]) instead of y
@@ -87,14 +88,11 @@ long long ffn_gather_rows(const Shape& s);
 size_t ffn_tile_meta_bytes(const Shape& s);
 size_t ffn_tile_claim_bytes(const Shape& s);
 
-// bf16 prefill: gathers the resident groups' token rows (and the batch in order,
-// for the shared experts) into a.xg, and packs the offloaded rows if asked;
-// must precede launch_grouped_ffn on the stream.  No-op on the other paths.
-hipError_t launch_gather_tokens(const Shape& s, const FfnArgs& a, hipStream_t st);
-
-// True when the FFN path packs the offloaded rows itself (in phase 1 at decode,
-// in the token gather at bf16 prefill).
-bool ffn_packs_offloaded(const Shape& s);
+// Prefill: writes the tables of the tiled FFN, packs the offloaded rows if asked, and for
+// bf16 gathers the resident groups' token rows (and the batch in order, for the shared
+// experts) into a.xg; must precede launch_grouped_ffn on the stream.  No-op at decode,
+// whose FFN phase 2 packs the offloaded rows.
+hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& a, hipStream_t st);
 
 // Number of K chunks the down projection is split into (1 = direct sums).
 int ffn_down_splits(const Shape& s);

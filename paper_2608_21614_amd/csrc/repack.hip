@@ -7,7 +7,7 @@
 // workgroups of 1024 threads; every workgroup counts the whole batch itself, so
 // none waits for another, and the result does not depend on the split.  A
 // second small kernel packs the offloaded rows for the host when the FFN does
-// not (moe_repack on its own, fp32 prefill).
+// not (moe_repack on its own).
 #include "block_ops.hpp"
 #include "kernels.hpp"
 

@@ -1,7 +1,7 @@
-"""The bf16 prefill FFN (tiled kernel) at the edges of its tiles, against the oracle:
-row counts around its token-block classes (64, 128, 192) and its 256-row token tile, more
-token tiles than one sweep takes, a single K slab pair, widths that leave half a weight
-tile, and more groups and items than workgroups start with."""
+"""The prefill FFN (tiled kernels) at the edges of its tiles, against the oracle: row counts
+around its token-block classes (bf16: 64, 128, 192; fp32: every 32) and its token tile (256
+and 128 rows), more token tiles than one sweep takes, a single K slab pair, widths that
+leave half a weight tile, and more groups and items than workgroups start with."""
 from __future__ import annotations
 
 import pytest
@@ -32,9 +32,13 @@ CASES = [(T, 128, 1, 64, 1, 0, 0, 1) for T in (65, 128, 129, 192, 193, 256, 257)
 ]
 
 
-@pytest.mark.parametrize("T,H,E,F,k,S,Fs,res", CASES)
-def test_tile_edges(moe, T, H, E, F, k, S, Fs, res):
-    print(f"[case] tiled T={T} H={H} E={E} F={F} k={k} S={S} Fs={Fs} resident={res}", flush=True)
-    lay = make_layer(T, H, E, F, k, dtype="bf16", shared=S, shared_ffn=Fs, n_resident=res, residency="random",
+F32_ROWS = [(T, 128, 1, 64, 1, 0, 0, 1) for T in (96, 97, 160, 161, 225, 289)]
+
+
+@pytest.mark.parametrize("dtype,T,H,E,F,k,S,Fs,res",
+                         [("bf16", *c) for c in CASES] + [("f32", *c) for c in CASES + F32_ROWS])
+def test_tile_edges(moe, dtype, T, H, E, F, k, S, Fs, res):
+    print(f"[case] tiled {dtype} T={T} H={H} E={E} F={F} k={k} S={S} Fs={Fs} resident={res}", flush=True)
+    lay = make_layer(T, H, E, F, k, dtype=dtype, shared=S, shared_ffn=Fs, n_resident=res, residency="random",
                      bias="zipf", seed=T + H)
     run_and_check_layer(moe, lay)
