@@ -4,53 +4,161 @@
 // Scores run on MFMA (v_mfma_f32_16x16x32_bf16, or v_mfma_f32_16x16x4_f32 for
 // fp32 inputs): router rows are the M side, 16 tokens the N side.
 //
-//  * T > 64 (prefill): k_route_topk, 8 tokens per 1024-thread workgroup whose
-//    16 waves split K and add their partial tiles in a fixed order.
-// The top-k takes one wave per token (topk_block: k rounds of a wave argmax).
+//  * T > 64 (prefill): k_router_scores, one workgroup per 16 tokens x 16, 32 or 64 experts
+//    whose 16 waves split K and add their partial tiles in a fixed order, writes the
+//    scores; then k_route_finish picks the top-k, one wave per token over many CUs.
 //  * T <= 64 (decode): k_router_partial spreads the scores over one workgroup
 //    per K slice (a single CU cannot stream the batch and the router fast
 //    enough), then k_route_finish adds each token's slices in order and runs its
-//    top-k, one wave per token over many CUs.  The fused forward and
-//    moe_route_topk use the same two kernels, so both give bit-identical scores;
-//    the repacking follows in k_repack.
+//    top-k.  The fused forward and moe_route_topk use the same two kernels, so both
+//    give bit-identical scores.
 #include "block_ops.hpp"
 #include "kernels.hpp"
 
 namespace saem {
 namespace {
 
-// Tokens per workgroup: 8 of the 16-token MFMA tile, so that a 2048-token batch fills all
-// 256 CUs (every workgroup streams the whole router matrix, whatever its token count).
-constexpr int kRouteRows = 8;
+// Top-k gate of token t by one wave, lane l holding the scores of experts l, l + 64, ...
+// (open: those that exist).  k rounds of a wave maximum over integer keys with the scores'
+// order, and a ballot per slot for the lowest id that has it.  The gate of choice j is
+// exp(s_j - s_0) / sum_j' exp(s_j' - s_0), summed in j order; a score equal to the top one
+// contributes exactly 1 (so all-equal rows, -inf included, get 1/k).  (NaN scores:
+// undefined selection, never an index outside [-1, E).)
+template <int NS>
+__device__ __forceinline__ void topk_wave(const float (&v)[NS], bool (&open)[NS], int k, int t,
+                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
+    const int lane = lane_id();
+    int key[NS];
+#pragma unroll
+    for (int sl = 0; sl < NS; ++sl) key[sl] = score_key(v[sl]);
+    float selv[8];
+    int sele[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        selv[j] = 0.f;
+        sele[j] = -1;
+        if (j >= k) continue;  // uniform
+        int kb = INT_MIN;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) kb = open[sl] ? max(kb, key[sl]) : kb;
+        const int m = wave_max_i32(kb);
+        // lowest id with that key: slot sl holds ids 64 sl .. 64 sl + 63, one per lane
+        int es = 0, el = 0;
+        bool found = false;  // always found in the end: k <= E
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) {
+            const unsigned long long b = __ballot(open[sl] && key[sl] == m);
+            if (!found && b) {
+                found = true;
+                es = sl;
+                el = __ffsll((long long)b) - 1;
+            }
+        }
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl)
+            if (es == sl && lane == el) open[sl] = false;
+        float ve = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), el));
+#pragma unroll
+        for (int sl = 1; sl < NS; ++sl)
+            if (es == sl) ve = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[sl]), el));
+        selv[j] = ve;
+        sele[j] = kWave * es + el;
+    }
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < k) sum += (selv[j] == selv[0]) ? 1.0f : expf(selv[j] - selv[0]);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (j < k && lane == j) {
+            const float term = (selv[j] == selv[0]) ? 1.0f : expf(selv[j] - selv[0]);
+            topk_idx[(size_t)t * k + j] = sele[j];
+            topk_w[(size_t)t * k + j] = term / sum;
+        }
+}
 
-template <bool kBf16>
-__global__ void __launch_bounds__(kFrontThreads)
-    k_route_topk(int T, int H, int E, int k, const void* __restrict__ x, const void* __restrict__ wr,
-                 const float* __restrict__ bias, float* __restrict__ logits, int logits_in,
-                 int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
-    __shared__ float s_lg[16 * kLgPitch];
-    __shared__ float s_red[kFrontWaves * 16 * kScoreChunk];
-    __shared__ float s_selv[64 * 8];
-    __shared__ int s_sele[64 * 8];
-    const int t0 = blockIdx.x * kRouteRows;
-    const int tend = min(T, t0 + kRouteRows);  // the MFMA tile's rows past it stay zero
-    if (!logits_in) {
-        if (kBf16)
-            router_scores_mfma<uint16_t, 1, kFrontWaves>(tend, H, E, static_cast<const uint16_t*>(x),
-                                                         static_cast<const uint16_t*>(wr), bias, t0, s_lg, s_red);
-        else
-            router_scores_mfma<float, 1, kFrontWaves>(tend, H, E, static_cast<const float*>(x),
-                                                      static_cast<const float*>(wr), bias, t0, s_lg, s_red);
+// Prefill scores of 16 tokens x 16 M experts by a workgroup of 16 waves; wave w takes the
+// 32-wide K steps w, w + 16, ...  Router rows are the MFMA M side, the tokens the N side;
+// the waves' partial tiles meet in LDS and are added in wave order, so the fp32 scores do
+// not depend on timing.
+//
+// Latency bounds it: a CU keeps about 64 KB of loads in flight, and a workgroup asks for
+// (tokens + experts) x H, so the tile is chosen by that (launch_prefill).  One kernel of 8
+// tokens a workgroup, each streaming the whole router, took 25 us at 150 tokens x 128
+// experts x H 2048 (19 workgroups), 14 to 16 at 2048 x 64, 53 at 8192 x 64 and 122 at 5305 x
+// 223 x H 2176; this one (with the top-k) takes 5.7 + 4.6, 14 to 16, 22 and 38 + 11.
+constexpr int kScoreWaves = 16;
+
+template <typename Elt, int M, int TT, bool kTopk>
+__global__ void __launch_bounds__(kScoreWaves* kWave)
+    k_router_scores(int T, int H, int E, int rows, const Elt* __restrict__ x, const Elt* __restrict__ wr,
+                    const float* __restrict__ bias, float* __restrict__ logits, int k, int32_t* __restrict__ topk_idx,
+                    float* __restrict__ topk_w) {
+    constexpr int U = (sizeof(Elt) == 2 ? 4 : 2) / TT;  // K steps per load batch
+    constexpr int kPitch = 16 * M + 4;  // floats of a partial row: the 16 row lanes' 16-byte writes spread over the banks
+    __shared__ __attribute__((aligned(16))) float red[kScoreWaves * 16 * TT * kPitch];
+    __shared__ float s_lg[kTopk ? 16 * TT : 1][kTopk ? 16 * M + 1 : 1];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    const int r = lane & 15, kq = (lane >> 4) * 8;
+    const int t0 = blockIdx.x * rows, e0 = blockIdx.y * 16 * M;
+    T = min(T, t0 + rows);  // rows <= 16 TT: the MFMA tile's rows past it stay zero
+    const Elt* xp[TT];
+    const Elt* wp[M];
+    f32x4 acc[TT][M];
+#pragma unroll
+    for (int j = 0; j < TT; ++j) xp[j] = (t0 + 16 * j + r < T) ? x + (size_t)(t0 + 16 * j + r) * H + kq : nullptr;
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        const int e = e0 + 16 * m + r;
+        wp[m] = (e < E) ? wr + (size_t)e * H + kq : nullptr;
+#pragma unroll
+        for (int j = 0; j < TT; ++j) acc[j][m] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int rows = tend - t0;
-    // scores <-> global, coalesced
-    for (int idx = threadIdx.x; idx < rows * E; idx += kFrontThreads) {
-        const int row = idx / E, e = idx % E;
-        if (logits_in) s_lg[row * kLgPitch + e] = logits[(size_t)(t0 + row) * E + e];
-        else logits[(size_t)(t0 + row) * E + e] = s_lg[row * kLgPitch + e];
+    const int nsteps = H / 32;
+    for (int i = wave; i < nsteps; i += U * kScoreWaves) {
+        Frag8<Elt> A[U][M], B[U][TT];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int s = i + kScoreWaves * u;
+            const bool ok = s < nsteps;
+#pragma unroll
+            for (int j = 0; j < TT; ++j) B[u][j] = (ok && xp[j]) ? load_frag(xp[j] + s * 32) : zero_frag<Elt>();
+#pragma unroll
+            for (int m = 0; m < M; ++m) A[u][m] = (ok && wp[m]) ? load_frag(wp[m] + s * 32) : zero_frag<Elt>();
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int j = 0; j < TT; ++j)
+#pragma unroll
+                for (int m = 0; m < M; ++m) acc[j][m] = mma_frag(A[u][m], B[u][j], acc[j][m]);
     }
+    // lane holds experts 16 m + 4 (lane / 16) + 0..3 of token row 16 j + r
+#pragma unroll
+    for (int j = 0; j < TT; ++j)
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+            *reinterpret_cast<f32x4*>(red + ((wave * TT + j) * 16 + r) * kPitch + 16 * m + 4 * (lane >> 4)) = acc[j][m];
     __syncthreads();
-    topk_block(s_lg, rows, E, k, t0, topk_idx, topk_w, nullptr, s_selv, s_sele);
+    for (int idx = threadIdx.x; idx < 16 * TT * 16 * M; idx += kScoreWaves * kWave) {
+        const int row = idx / (16 * M), el = idx % (16 * M);
+        const int t = t0 + row, e = e0 + el;
+        if (t >= T || e >= E) continue;
+        float v = red[row * kPitch + el];
+#pragma unroll
+        for (int p = 1; p < kScoreWaves; ++p) v += red[(p * 16 * TT + row) * kPitch + el];
+        v += bias ? bias[e] : 0.f;
+        logits[(size_t)t * E + e] = v;
+        if constexpr (kTopk) s_lg[row][el] = v;
+    }
+    if constexpr (kTopk) {
+        __syncthreads();
+        for (int row = wave; row < 16 * TT && t0 + row < T; row += kScoreWaves) {
+            bool open[1] = {lane < E};
+            const float v[1] = {lane < E ? s_lg[row][lane] : 0.f};
+            topk_wave<1>(v, open, k, t0 + row, topk_idx, topk_w);
+        }
+    }
 }
 
 // Decode batches: part[slice][t][e] = sum over the slice's K steps of x[t] . w_router[e].
@@ -106,32 +214,26 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// Decode front end, second step: one wave per token adds the token's K-sliced
-// partial scores in slice order (+ bias) and writes them to logits (or reads the
-// caller's scores), then picks the token's top-k in rank order with k rounds of
-// a wave argmax over integer keys with the scores' order: lane l holds experts
-// l, l + 64, l + 128, l + 192, offers its best open one (largest key, then lowest
-// id), and the wave takes the largest key and, among the lanes offering it, the
-// lowest id.  The gate of choice j is exp(s_j - s_0) / sum_j' exp(s_j' - s_0),
-// summed in j order; a score equal to the top one contributes exactly 1.
-// NS: expert slots per lane (E <= 64 NS).
-template <int NS>
+// Top-k gate, one wave per token.  At decode the wave first adds the token's K-sliced
+// partial scores in slice order (+ bias) and writes them to logits; at prefill, and with
+// the caller's scores, it reads logits.
+// NS: expert slots per lane (E <= 64 NS).  kLogitsIn: the scores are in logits (without the
+// slices' registers a CU holds two to four times the waves).
+template <int NS, bool kLogitsIn>
 __global__ void __launch_bounds__(256)
     k_route_finish(int T, int E, int k, const float* __restrict__ part, int nsl, const float* __restrict__ bias,
-                   float* __restrict__ logits, int logits_in, int32_t* __restrict__ topk_idx,
-                   float* __restrict__ topk_w) {
+                   float* __restrict__ logits, int32_t* __restrict__ topk_idx, float* __restrict__ topk_w) {
     const int lane = lane_id();
     const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= T) return;  // the whole wave
     float v[NS];
-    int key[NS];
     bool open[NS];
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {
         open[sl] = lane + kWave * sl < E;
         v[sl] = 0.f;
     }
-    if (logits_in) {
+    if constexpr (kLogitsIn) {
 #pragma unroll
         for (int sl = 0; sl < NS; ++sl)
             if (open[sl]) v[sl] = logits[(size_t)t * E + lane + kWave * sl];
@@ -161,71 +263,58 @@ __global__ void __launch_bounds__(256)
                 logits[(size_t)t * E + lane + kWave * sl] = v[sl];
             }
     }
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) key[sl] = score_key(v[sl]);
-    float selv[8];
-    int sele[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        selv[j] = 0.f;
-        sele[j] = -1;
-        if (j >= k) continue;  // uniform
-        int kb = INT_MIN, eb = INT_MAX;
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl)
-            if (open[sl] && (eb == INT_MAX || key[sl] > kb)) {
-                kb = key[sl];
-                eb = lane + kWave * sl;
-            }
-        const int m = wave_max_i32(eb != INT_MAX ? kb : INT_MIN);
-        const int e = wave_min_i32((eb != INT_MAX && kb == m) ? eb : INT_MAX);  // never INT_MAX: k <= E
-#pragma unroll
-        for (int sl = 0; sl < NS; ++sl)
-            if (lane + kWave * sl == e) open[sl] = false;
-        const int es = e >> 6, el = e & 63;
-        float ve = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), el));
-#pragma unroll
-        for (int sl = 1; sl < NS; ++sl)
-            if (es == sl) ve = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[sl]), el));
-        selv[j] = ve;
-        sele[j] = e;
-    }
-    float sum = 0.f;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < k) sum += (selv[j] == selv[0]) ? 1.0f : expf(selv[j] - selv[0]);
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < k && lane == j) {
-            const float term = (selv[j] == selv[0]) ? 1.0f : expf(selv[j] - selv[0]);
-            topk_idx[(size_t)t * k + j] = sele[j];
-            topk_w[(size_t)t * k + j] = term / sum;
-        }
+    topk_wave<NS>(v, open, k, t, topk_idx, topk_w);
 }
 
-hipError_t launch_small(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
-                        bool logits_in, int32_t* topk_idx, float* topk_w, float* part, hipStream_t st) {
-    const int nsl = router_slices(s);
-    if (!logits_in && s.T > 0) {
-        if (s.bf16)
-            hipLaunchKernelGGL(k_router_partial<uint16_t>, dim3(nsl, (s.E + kScoreChunk - 1) / kScoreChunk), dim3(256),
-                               0, st, s.T, s.H, s.E, x, w_router, nsl, part);
-        else
-            hipLaunchKernelGGL(k_router_partial<float>, dim3(nsl, (s.E + kScoreChunk - 1) / kScoreChunk), dim3(256), 0,
-                               st, s.T, s.H, s.E, x, w_router, nsl, part);
-    }
+void launch_finish(const Shape& s, const float* part, int nsl, const float* bias, float* logits, bool logits_in,
+                   int32_t* topk_idx, float* topk_w, hipStream_t st) {
     const dim3 grid((s.T + 3) / 4);
-    const int li = logits_in ? 1 : 0;
-    if (s.E <= 64)
-        hipLaunchKernelGGL(k_route_finish<1>, grid, dim3(256), 0, st, s.T, s.E, s.k, part, nsl, bias, logits, li,
-                           topk_idx, topk_w);
-    else if (s.E <= 128)
-        hipLaunchKernelGGL(k_route_finish<2>, grid, dim3(256), 0, st, s.T, s.E, s.k, part, nsl, bias, logits, li,
-                           topk_idx, topk_w);
-    else
-        hipLaunchKernelGGL(k_route_finish<4>, grid, dim3(256), 0, st, s.T, s.E, s.k, part, nsl, bias, logits, li,
-                           topk_idx, topk_w);
-    return hipGetLastError();
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, s.T, s.E, s.k, part, nsl, bias, logits, topk_idx, topk_w);
+    };
+    if (s.E <= 64) logits_in ? go(k_route_finish<1, true>) : go(k_route_finish<1, false>);
+    else if (s.E <= 128) logits_in ? go(k_route_finish<2, true>) : go(k_route_finish<2, false>);
+    else logits_in ? go(k_route_finish<4, true>) : go(k_route_finish<4, false>);
+}
+
+// Prefill routing.  A CU draws about 64 KB per microsecond of such loads, so what counts is
+// the bytes of the fullest CU: (tokens + experts of a workgroup) x H.
+//  * Up to 64 experts a workgroup has all scores of its tokens and picks their top-k itself,
+//    for 8 tokens (half an MFMA tile) while that leaves at most 512 workgroups, then 16 or
+//    32.  At 8192 x 64 x H 2048, 32 tokens take 22 us; two launches take 16 + 8 + the gap.
+//  * With 17 to 64 experts whose rows are long (8 KB or more) and fewer than 4096 tokens, the
+//    smaller loads of 16 tokens x 32 experts pay for the second launch: 2048 x 64 x H 2048
+//    in fp32 14.0 + 4.6 us against 25.4 (in bf16 8.4 + 4.7 + the gap against 14).
+//  * More than 64 experts: the largest tile that still gives every CU a workgroup, then the
+//    top-k in a launch of its own.
+template <typename Elt>
+void launch_prefill(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
+                    int32_t* topk_idx, float* topk_w, hipStream_t st) {
+    auto tiles = [&](int n, int tile) { return (n + tile - 1) / tile; };
+    auto go = [&](auto kernel, int rows, int m) {
+        hipLaunchKernelGGL(kernel, dim3(tiles(s.T, rows), tiles(s.E, 16 * m)), dim3(kScoreWaves * kWave), 0, st, s.T,
+                           s.H, s.E, rows, static_cast<const Elt*>(x), static_cast<const Elt*>(w_router), bias, logits,
+                           s.k, topk_idx, topk_w);
+    };
+    const bool long_rows = (size_t)s.H * sizeof(Elt) >= 8192;
+    if (s.E <= 16 || (s.E <= 64 && (s.T >= 4096 || !long_rows))) {
+        const int rows = s.T >= 8192 ? 32 : (s.T >= 4096 ? 16 : 8);
+        if (rows == 32) {
+            if (s.E <= 16) go(k_router_scores<Elt, 1, 2, true>, rows, 1);
+            else if (s.E <= 32) go(k_router_scores<Elt, 2, 2, true>, rows, 2);
+            else go(k_router_scores<Elt, 4, 2, true>, rows, 4);
+        } else {
+            if (s.E <= 16) go(k_router_scores<Elt, 1, 1, true>, rows, 1);
+            else if (s.E <= 32) go(k_router_scores<Elt, 2, 1, true>, rows, 2);
+            else go(k_router_scores<Elt, 4, 1, true>, rows, 4);
+        }
+        return;
+    }
+    if (tiles(s.T, 32) * tiles(s.E, 64) >= 256) go(k_router_scores<Elt, 4, 2, false>, 32, 4);
+    else if (tiles(s.T, 16) * tiles(s.E, 64) >= 256) go(k_router_scores<Elt, 4, 1, false>, 16, 4);
+    else if (tiles(s.T, 16) * tiles(s.E, 32) >= 256) go(k_router_scores<Elt, 2, 1, false>, 16, 2);
+    else go(k_router_scores<Elt, 1, 1, false>, 16, 1);
+    launch_finish(s, nullptr, 0, nullptr, logits, true, topk_idx, topk_w, st);
 }
 
 }  // namespace
@@ -241,15 +330,20 @@ int router_slices(const Shape& s) {
 hipError_t launch_route_topk(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
                              bool logits_in, int32_t* topk_idx, float* topk_w, float* part, hipStream_t st) {
     if (s.T == 0) return hipSuccess;
-    if (front_small_fits(s)) return launch_small(s, x, w_router, bias, logits, logits_in, topk_idx, topk_w, part, st);
-    const int li = logits_in ? 1 : 0;
-    dim3 grid((s.T + kRouteRows - 1) / kRouteRows), block(kFrontThreads);
-    if (s.bf16)
-        hipLaunchKernelGGL(k_route_topk<true>, grid, block, 0, st, s.T, s.H, s.E, s.k, x, w_router, bias, logits, li,
-                           topk_idx, topk_w);
-    else
-        hipLaunchKernelGGL(k_route_topk<false>, grid, block, 0, st, s.T, s.H, s.E, s.k, x, w_router, bias, logits,
-                           li, topk_idx, topk_w);
+    if (!front_small_fits(s)) {
+        if (logits_in) launch_finish(s, nullptr, 0, nullptr, logits, true, topk_idx, topk_w, st);
+        else if (s.bf16) launch_prefill<uint16_t>(s, x, w_router, bias, logits, topk_idx, topk_w, st);
+        else launch_prefill<float>(s, x, w_router, bias, logits, topk_idx, topk_w, st);
+        return hipGetLastError();
+    }
+    const int nsl = router_slices(s);
+    if (!logits_in) {
+        const dim3 grid(nsl, (s.E + kScoreChunk - 1) / kScoreChunk);
+        if (s.bf16)
+            hipLaunchKernelGGL(k_router_partial<uint16_t>, grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl, part);
+        else hipLaunchKernelGGL(k_router_partial<float>, grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl, part);
+    }
+    launch_finish(s, part, nsl, bias, logits, logits_in, topk_idx, topk_w, st);
     return hipGetLastError();
 }
 
