@@ -201,15 +201,13 @@ moe_status moe_grouped_ffn(const moe_dims* dims, const void* x, const int32_t* p
     a.Fa = L.Fa;
     a.ks = L.ks;
     a.y_ks_stride = L.rows * (long long)s.H;
-    // the expert outputs go straight to y unless they are split-K partial sums or bf16 rows,
-    // which are added (widened) into y afterwards, resident and shared rows only
-    const bool y16 = saem::ffn_y_bf16(s);
-    a.y = (L.ks == 1 && !y16) ? y : at<float>(ws, L.y);
-    a.y16 = y16 ? at<char>(ws, L.y) : nullptr;
+    // the expert outputs go straight to y unless they are split-K partial sums, which are
+    // added into y afterwards, resident and shared rows only
+    a.y = L.ks == 1 ? y : at<float>(ws, L.y);
     hipError_t e = saem::launch_ffn_prepare(s, a, hs);
     if (e == hipSuccess) e = saem::launch_grouped_ffn(s, a, hs);
-    if (e == hipSuccess && (L.ks > 1 || y16))
-        e = saem::launch_reduce_splits(s, counts, expert_slot, y16 ? a.y16 : a.y, y16, L.ks, a.y_ks_stride, y, hs);
+    if (e == hipSuccess && L.ks > 1)
+        e = saem::launch_reduce_splits(s, counts, expert_slot, a.y, L.ks, a.y_ks_stride, y, hs);
     return hip_status(e);
 }
 

@@ -81,7 +81,7 @@ struct Args {
     int32_t* tmeta;   // prefill: tables of the tiled kernels
     int tcap1;        // capacity of the phase-1 table
     int32_t* tclaim;  // prefill: claim counters of the tiled kernels, eight per phase
-    uint16_t* y16;    // bf16 prefill: expert outputs [rows][H] in bf16 (instead of y)
+    uint16_t* y16;    // bf16 prefill: expert outputs [rows][H] in bf16; null: the same values in y
     // decode with the repacking in phase 1 (fused): the ids, and the repack's outputs
     int fused;
     int slot_items;   // fused phase 1: routed item gi is slot gi's expert (every slot can be active)
@@ -1182,14 +1182,22 @@ __global__ void __launch_bounds__(256, 2)
                 *reinterpret_cast<u32x4*>(act + ((size_t)(blk >> 1) * (a.Fa / 32) + (blk & 1)) * 512 + 8 * piece) = v;
             }
         } else {
-            // the group's rows x 16 pieces of 16 bytes; outputs that exist
+            // the group's rows x 16 pieces of 8 outputs, those that exist: bf16 rows for the
+            // combine, or (moe_grouped_ffn on its own) the same values widened into y, where a
+            // pass of its own that widened bf16 rows moved half the bytes again
             const int rows = min(kTN, tg.count - n0);
-            uint16_t* y = a.y16 + (size_t)(tg.rowbase + n0) * a.H + r0;
+            const size_t at = (size_t)(tg.rowbase + n0) * a.H + r0;
             for (int c = tid; c < rows * 16; c += 256) {
                 const int nl = c >> 4, piece = c & 15;
                 if (r0 + 8 * piece >= a.H) continue;
                 const u32x4 v = *reinterpret_cast<const u32x4*>(sbuf + (nl * kTPitch + 8 * piece) * 2);
-                *reinterpret_cast<u32x4*>(y + (size_t)nl * a.H + 8 * piece) = v;
+                const size_t to = at + (size_t)nl * a.H + 8 * piece;
+                if (a.y16) {
+                    *reinterpret_cast<u32x4*>(a.y16 + to) = v;
+                } else {
+                    *reinterpret_cast<f32x4*>(a.y + to) = bf16x4_to_f32(u32x2{v.x, v.y});
+                    *reinterpret_cast<f32x4*>(a.y + to + 4) = bf16x4_to_f32(u32x2{v.z, v.w});
+                }
             }
         }
         __syncthreads();  // the epilogue is done with the LDS
@@ -1471,33 +1479,24 @@ __global__ void __launch_bounds__(256, 2)
     }
 }
 
-// y_out[p] = sum_c y[c][p] for resident packed rows p < n_res and all shared rows
-// (kInBf16: a single chunk of bf16 rows, widened).
-template <bool kInBf16>
+// y_out[p] = sum_c y[c][p] for resident packed rows p < n_res and all shared rows.
 __global__ void __launch_bounds__(256) k_reduce_splits(int T, int H, int E, int k, int S, int slots,
                                                        const int32_t* __restrict__ counts,
                                                        const int32_t* __restrict__ expert_slot,
-                                                       const void* __restrict__ y_in, int ks, long long stride,
+                                                       const float* __restrict__ y, int ks, long long stride,
                                                        float* __restrict__ y_out) {
-    __shared__ int s_nres;
-    if (threadIdx.x == 0) {
-        int n = 0;
-        for (int e = 0; e < E; ++e)
-            if (is_resident(expert_slot[e], slots)) n += counts[e] > 0 ? counts[e] : 0;
-        s_nres = n;
-    }
+    // every row's workgroup adds up n_res itself, one expert per thread
+    __shared__ int s_sum[4];
+    int n = 0;
+    if ((int)threadIdx.x < E && is_resident(expert_slot[threadIdx.x], slots)) n = max(counts[threadIdx.x], 0);
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) n += __shfl_xor(n, off, kWave);
+    if (lane_id() == 0) s_sum[threadIdx.x >> 6] = n;
     __syncthreads();
-    const int P = T * k, rows = P + S * T;
+    const int nres = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
+    const int P = T * k;
     const int row = blockIdx.x;
-    if (row >= rows || (row < P && row >= s_nres)) return;
-    if constexpr (kInBf16) {
-        const uint16_t* y = static_cast<const uint16_t*>(y_in);
-        for (int h = threadIdx.x * 4; h < H; h += 1024)
-            *reinterpret_cast<f32x4*>(y_out + (size_t)row * H + h) =
-                bf16x4_to_f32(*reinterpret_cast<const u32x2*>(y + (size_t)row * H + h));
-        return;
-    }
-    const float* y = static_cast<const float*>(y_in);
+    if (row < P && row >= nres) return;
     for (int h = threadIdx.x * 4; h < H; h += 1024) {
         constexpr int kMax = 16;  // same order as the combine: chunk 0, then 1, ...
         f32x4 p[kMax];
@@ -1730,16 +1729,12 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
     return hipGetLastError();
 }
 
-hipError_t launch_reduce_splits(const Shape& s, const int32_t* counts, const int32_t* expert_slot, const void* y,
-                                bool y_bf16, int ks, long long y_ks_stride, float* y_out, hipStream_t st) {
+hipError_t launch_reduce_splits(const Shape& s, const int32_t* counts, const int32_t* expert_slot, const float* y,
+                                int ks, long long y_ks_stride, float* y_out, hipStream_t st) {
     const int rows = s.T * s.k + s.S * s.T;
     if (rows == 0) return hipSuccess;
-    if (y_bf16)
-        hipLaunchKernelGGL(k_reduce_splits<true>, dim3(rows), dim3(256), 0, st, s.T, s.H, s.E, s.k, s.S, s.slots,
-                           counts, expert_slot, y, 1, y_ks_stride, y_out);
-    else
-        hipLaunchKernelGGL(k_reduce_splits<false>, dim3(rows), dim3(256), 0, st, s.T, s.H, s.E, s.k, s.S, s.slots,
-                           counts, expert_slot, y, ks, y_ks_stride, y_out);
+    hipLaunchKernelGGL(k_reduce_splits, dim3(rows), dim3(256), 0, st, s.T, s.H, s.E, s.k, s.S, s.slots, counts,
+                       expert_slot, y, ks, y_ks_stride, y_out);
     return hipGetLastError();
 }
 

@@ -59,7 +59,8 @@ struct FfnArgs {
     // group), 32-byte aligned, and
     int32_t* tmeta = nullptr;
     int32_t* tclaim = nullptr;  // the tiled kernels' claim counters (ffn_tile_claim_bytes(s))
-    // bf16 prefill: phase 2 writes the expert outputs here in bf16 ([rows][H]) instead of y
+    // bf16 prefill: phase 2 writes the expert outputs here in bf16 ([rows][H]); without it the
+    // same values widened into y
     void* y16 = nullptr;
     // decode (ffn_fuses_repack): phase 1 takes the repacking over from topk_idx. Its
     // workgroups derive their groups from the ids, one more workgroup writes counts,
@@ -99,10 +100,9 @@ int ffn_down_splits(const Shape& s);
 // Launches phase 1 then phase 2; records `between` (if not null) after phase 1.
 hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& a, hipStream_t st, hipEvent_t between = nullptr);
 
-// y_out[p] = sum_c y[c][p] for the resident packed rows and the shared rows (y_bf16:
-// one chunk of bf16 rows, widened to fp32).
-hipError_t launch_reduce_splits(const Shape& s, const int32_t* counts, const int32_t* expert_slot, const void* y,
-                                bool y_bf16, int ks, long long y_ks_stride, float* y_out, hipStream_t st);
+// y_out[p] = sum_c y[c][p] for the resident packed rows and the shared rows.
+hipError_t launch_reduce_splits(const Shape& s, const int32_t* counts, const int32_t* expert_slot, const float* y,
+                                int ks, long long y_ks_stride, float* y_out, hipStream_t st);
 
 // Deterministic combine back to token order.  y: ks fp32 chunks, or (y_bf16) one chunk of bf16 rows.
 hipError_t launch_combine(const Shape& s, const int32_t* topk_idx, const float* topk_w, const int32_t* inv_perm,
