@@ -171,8 +171,8 @@ moe_status moe_repack(const moe_dims* dims, const int32_t* topk_idx, const float
     if (off_w && !ok_arr4(topk_w, T)) return MOE_ERR_INVALID_ARG;
     const Shape s = shape_of(dims);
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    hipError_t e = saem::launch_repack(s, topk_idx, expert_slot, counts, seg_start, perm, inv_perm, n_res, hs);
-    if (e == hipSuccess) e = saem::launch_offload_pack(s, x, topk_w, perm, n_res, off_rows, off_w, hs);
+    const hipError_t e = saem::launch_repack(s, topk_idx, expert_slot, counts, seg_start, perm, inv_perm, n_res, x,
+                                             topk_w, off_rows, off_w, hs);
     return hip_status(e);
 }
 
@@ -279,7 +279,8 @@ static moe_status layer_forward(const moe_layer_args* a, void* ws, size_t ws_byt
     const bool fuse_repack = saem::ffn_fuses_repack(s);
     if (e == hipSuccess)
         e = mark(fuse_repack ? hipSuccess
-                             : saem::launch_repack(s, idx, a->expert_slot, counts, seg, perm, inv, nres, hs),
+                             : saem::launch_repack(s, idx, a->expert_slot, counts, seg, perm, inv, nres, nullptr, nullptr,
+                                                   nullptr, nullptr, hs),
                  2);
     if (s.T == 0) {
         for (int i = 3; i < MOE_STAGE_EVENTS && e == hipSuccess; ++i) e = mark(hipSuccess, i);

@@ -57,12 +57,14 @@ constexpr int repack_lds_ints() {
 // The workgroup with c_begin == 0 also writes counts, seg_start and n_res.
 // ids outside [0, E) are dropped (inv_perm = -1); the packed rows they leave
 // over at the end, [sum(counts), T*k), get perm = -1.
-template <int NT>
-__device__ inline void repack_chunks(int T, int E, int k, int slots, int c_begin, int c_end,
+// kLocal: nothing is written to memory; the workgroup takes all chunks and leaves the
+// permutation in s_perm (T*k ints of LDS), for its own use.  Returns n_res.
+template <int NT, bool kLocal = false>
+__device__ inline int repack_chunks(int T, int E, int k, int slots, int c_begin, int c_end,
                                      const int32_t* __restrict__ idx, const int32_t* __restrict__ expert_slot,
                                      int32_t* __restrict__ counts, int32_t* __restrict__ seg_start,
                                      int32_t* __restrict__ perm, int32_t* __restrict__ inv_perm,
-                                     int32_t* __restrict__ n_res, int* lds) {
+                                     int32_t* __restrict__ n_res, int* lds, int* s_perm = nullptr) {
     int* s_cnt = lds;
     int* s_pre = lds + 256;
     int* s_base = lds + 512;
@@ -130,7 +132,10 @@ __device__ inline void repack_chunks(int T, int E, int k, int slots, int c_begin
         }
     }
     __syncthreads();
-    if (c_begin == 0) {
+    const int total_res = s_nres[0];
+    if (kLocal) {
+        for (int p = s_nres[1] + tid; p < P; p += NT) s_perm[p] = -1;
+    } else if (c_begin == 0) {
         for (int e = tid; e < E; e += NT) {
             counts[e] = s_cnt[e];
             seg_start[e] = s_base[e];
@@ -162,9 +167,13 @@ __device__ inline void repack_chunks(int T, int E, int k, int slots, int c_begin
         if (valid) {
             int p = s_base[e] + rank;
             for (int w = 0; w < wave; ++w) p += s_wcnt[w * 256 + e];
-            perm[p] = q;
-            inv_perm[q] = p;
-        } else if (q < P) {
+            if (kLocal) {
+                s_perm[p] = q;
+            } else {
+                perm[p] = q;
+                inv_perm[q] = p;
+            }
+        } else if (q < P && !kLocal) {
             inv_perm[q] = -1;
         }
         __syncthreads();
@@ -176,6 +185,7 @@ __device__ inline void repack_chunks(int T, int E, int k, int slots, int c_begin
         }
         __syncthreads();
     }
+    return total_res;
 }
 
 }  // namespace saem

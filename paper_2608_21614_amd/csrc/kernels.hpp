@@ -22,14 +22,12 @@ int router_slices(const Shape& s);
 hipError_t launch_route_topk(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
                              bool logits_in, int32_t* topk_idx, float* topk_w, float* part, hipStream_t st);
 
-// Expert-aligned repacking: histogram, group-order scan, stable permutation,
-// residency split (one workgroup).
+// Expert-aligned repacking: histogram, group-order scan, stable permutation, residency
+// split; and, if off_rows or off_w is given, the offloaded pairs' rows and gates:
+// off_rows[p - n_res] = x[perm[p] / k], off_w[p - n_res] = topk_w[perm[p]].
 hipError_t launch_repack(const Shape& s, const int32_t* topk_idx, const int32_t* expert_slot, int32_t* counts,
-                         int32_t* seg_start, int32_t* perm, int32_t* inv_perm, int32_t* n_res, hipStream_t st);
-
-// Packs the rows of the offloaded pairs: off_rows[p - n_res] = x[perm[p] / k], off_w[p - n_res] = w[perm[p]].
-hipError_t launch_offload_pack(const Shape& s, const void* x, const float* topk_w, const int32_t* perm,
-                               const int32_t* n_res, void* off_rows, float* off_w, hipStream_t st);
+                         int32_t* seg_start, int32_t* perm, int32_t* inv_perm, int32_t* n_res, const void* x,
+                         const float* topk_w, void* off_rows, float* off_w, hipStream_t st);
 
 // Grouped SwiGLU FFN.  Row space: packed rows [0, T*k) then shared rows T*k + s*T + t.
 struct FfnArgs {
