@@ -11,7 +11,6 @@
 namespace saem {
 
 constexpr int kFrontThreads = 1024;            // 16 waves
-constexpr int kScoreChunk = 64;                 // experts (4 MFMA row tiles) per decode router workgroup
 
 // Integer key with the order of the float scores: equal keys iff equal scores
 // (-0 is folded into +0), larger key iff larger score.

@@ -162,12 +162,18 @@ __global__ void __launch_bounds__(kScoreWaves* kWave)
 }
 
 // Decode batches: part[slice][t][e] = sum over the slice's K steps of x[t] . w_router[e].
-// One workgroup per (K slice, chunk of 64 experts); wave w covers tokens
-// 16w .. 16w+15; MFMA on bf16 (16x16x32) or fp32 (16x16x4) operands.
+// One workgroup per (K slice, chunk of 16 kPartM experts); wave w covers tokens
+// 16w .. 16w+15; MFMA on bf16 (16x16x32) or fp32 (16x16x4) operands.  Latency bounds it, and a
+// CU keeps about 64 KB of loads in flight, which a workgroup with 64 experts exceeds: chunks of
+// 64 / 32 / 16 experts take 7.2 / 4.8 / 4.7 us for 64 tokens x 128 experts x H 2048, 6.4 / 4.7 /
+// 4.7 for 64 x 60, 4.8 / 3.4 / 2.8 for one token x 128.
+constexpr int kPartM = 1;
+
 template <typename Elt>
 __global__ void __launch_bounds__(256)
     k_router_partial(int T, int H, int E, const void* __restrict__ x, const void* __restrict__ wr, int nsl,
                      float* __restrict__ part) {
+    constexpr int M = kPartM;
     const int slice = blockIdx.x;
     const int nst = H / 32, s0 = slice * nst / nsl, s1 = (slice + 1) * nst / nsl;
     float* out = part + (size_t)slice * 64 * E;
@@ -176,41 +182,38 @@ __global__ void __launch_bounds__(256)
     if (16 * wave >= T) return;
     const int tok = 16 * wave + r;
     const Elt* xp = (tok < T) ? static_cast<const Elt*>(x) + (size_t)tok * H + kq : nullptr;
-    {
-        const int c0 = blockIdx.y * kScoreChunk;
-        f32x4 acc[4];
-        const Elt* wp[4];
+    const int c0 = blockIdx.y * 16 * M;
+    f32x4 acc[M];
+    const Elt* wp[M];
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-            acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int e = c0 + 16 * m + r;
-            wp[m] = (e < E) ? static_cast<const Elt*>(wr) + (size_t)e * H + kq : nullptr;
+    for (int m = 0; m < M; ++m) {
+        acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int e = c0 + 16 * m + r;
+        wp[m] = (e < E) ? static_cast<const Elt*>(wr) + (size_t)e * H + kq : nullptr;
+    }
+    for (int s = s0; s < s1; s += 4) {
+        Frag8<Elt> A[4][M], B[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const bool ok = s + u < s1;
+            B[u] = (ok && xp) ? load_frag(xp + (s + u) * 32) : zero_frag<Elt>();
+#pragma unroll
+            for (int m = 0; m < M; ++m) A[u][m] = (ok && wp[m]) ? load_frag(wp[m] + (s + u) * 32) : zero_frag<Elt>();
         }
-        for (int s = s0; s < s1; s += 4) {
-            Frag8<Elt> A[4][4], B[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const bool ok = s + u < s1;
-                B[u] = (ok && xp) ? load_frag(xp + (s + u) * 32) : zero_frag<Elt>();
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    A[u][m] = (ok && wp[m]) ? load_frag(wp[m] + (s + u) * 32) : zero_frag<Elt>();
+            for (int m = 0; m < M; ++m)
+                if (c0 + 16 * m < E) acc[m] = mma_frag(A[u][m], B[u], acc[m]);
+    }
+    if (tok < T) {
+#pragma unroll
+        for (int m = 0; m < M; ++m)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int e = c0 + 16 * m + 4 * (lane >> 4) + i;
+                if (e < E) out[tok * E + e] = acc[m][i];
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    if (c0 + 16 * m < E) acc[m] = mma_frag(A[u][m], B[u], acc[m]);
-        }
-        if (tok < T) {
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = c0 + 16 * m + 4 * (lane >> 4) + i;
-                    if (e < E) out[tok * E + e] = acc[m][i];
-                }
-        }
     }
 }
 
@@ -338,10 +341,13 @@ hipError_t launch_route_topk(const Shape& s, const void* x, const void* w_router
     }
     const int nsl = router_slices(s);
     if (!logits_in) {
-        const dim3 grid(nsl, (s.E + kScoreChunk - 1) / kScoreChunk);
+        const dim3 grid(nsl, (s.E + 16 * kPartM - 1) / (16 * kPartM));
         if (s.bf16)
-            hipLaunchKernelGGL(k_router_partial<uint16_t>, grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl, part);
-        else hipLaunchKernelGGL(k_router_partial<float>, grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl, part);
+            hipLaunchKernelGGL((k_router_partial<uint16_t>), grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl,
+                               part);
+        else
+            hipLaunchKernelGGL((k_router_partial<float>), grid, dim3(256), 0, st, s.T, s.H, s.E, x, w_router, nsl,
+                               part);
     }
     launch_finish(s, part, nsl, bias, logits, logits_in, topk_idx, topk_w, st);
     return hipGetLastError();
