@@ -15,29 +15,43 @@
 namespace saem {
 namespace {
 
-// One thread moves 8 consecutive K elements of one row (elt = 2 or 4 bytes).
+// One thread moves 8 consecutive K elements of one row in each of two neighbouring blocks (elt =
+// 2 or 4 bytes), so that a wave reads whole 128-byte lines of the rows; the stores, whose
+// lines nothing reads soon, are non-temporal.  HBM bounds it: one expert of H 4096, F 14336
+// (352 MB read, 352 MB written) took 128.6 us with half lines and plain stores, 122.3 with
+// non-temporal stores, 121.3 with both; non-temporal loads as well: 131.
 template <typename T>
 __global__ void __launch_bounds__(256)
     k_pack(const T* __restrict__ src, T* __restrict__ dst, long long rows, long long K) {
-    const long long nsteps = K / 32;
-    const long long chunks = rows * (K / 8);  // 8-element chunks
-    for (long long c = (long long)blockIdx.x * 256 + threadIdx.x; c < chunks; c += (long long)gridDim.x * 256) {
-        const long long blk = c / 64, l = c % 64;
-        const long long rt = blk / nsteps, s = blk % nsteps;
-        const long long row = 16 * rt + (l & 15), col = 32 * s + 8 * (l >> 4);
-        const T* in = src + row * K + col;
-        T* out = dst + blk * 512 + l * 8;
+    constexpr int kV = (int)sizeof(T) / 2;  // 16-byte pieces of 8 elements
+    const long long nsteps = K / 32, pairs = (nsteps + 1) / 2;
+    const long long work = rows / 16 * pairs * 64;
+    for (long long c = (long long)blockIdx.x * 256 + threadIdx.x; c < work; c += (long long)gridDim.x * 256) {
+        const long long p = c / 64, l = c % 64;
+        const long long rt = p / pairs, s = 2 * (p % pairs);
+        const bool two = s + 1 < nsteps;
+        const u32x4* in = reinterpret_cast<const u32x4*>(src + (16 * rt + (l & 15)) * K + 32 * s + 8 * (l >> 4));
+        u32x4* out = reinterpret_cast<u32x4*>(dst + (rt * nsteps + s) * 512 + l * 8);
+        u32x4 v[2][kV];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = in[i];
+        for (int i = 0; i < kV; ++i) {
+            v[0][i] = in[i];
+            if (two) v[1][i] = in[4 * kV + i];
+        }
+#pragma unroll
+        for (int i = 0; i < kV; ++i) {
+            __builtin_nontemporal_store(v[0][i], out + i);
+            if (two) __builtin_nontemporal_store(v[1][i], out + 64 * kV + i);
+        }
     }
 }
 
 }  // namespace
 
 hipError_t launch_pack_weights(const void* src, void* dst, long long rows, long long K, bool bf16, hipStream_t st) {
-    const long long chunks = rows * (K / 8);
-    if (chunks == 0) return hipSuccess;
-    long long grid = (chunks + 255) / 256;
+    const long long work = rows / 16 * ((K / 32 + 1) / 2) * 64;
+    if (work == 0) return hipSuccess;
+    long long grid = (work + 255) / 256;
     if (grid > 65536) grid = 65536;
     if (bf16)
         hipLaunchKernelGGL(k_pack<uint16_t>, dim3((unsigned)grid), dim3(256), 0, st, static_cast<const uint16_t*>(src),
