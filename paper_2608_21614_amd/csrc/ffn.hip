@@ -676,13 +676,19 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
 // waves on 32x32x16, one workgroup per CU) and now, phase 1 / phase 2 in us, bf16:
 //   64 experts x 1024 rows, H 2048, F 1408:   680 / 384 -> 618 / 363
 //   48 experts x  256 rows, H 2048, F 1408:   184 /  95 -> 161 /  91
-//   48 experts x  100 rows, H 2048, F 1408:   158 /  82 -> 128 /  69
-//   48 experts x   40 rows, H 2048, F 1408:   140 /  72 -> 108 /  66
-//    8 experts x   83 rows, H 4096, F 14336:  386 / 284 -> 352 / 169
-//   64 experts x   16 rows, H 2048, F 768:     93 /  50 ->  72 /  42
+//   48 experts x  100 rows, H 2048, F 1408:   158 /  82 -> 126 /  69
+//   48 experts x   40 rows, H 2048, F 1408:   140 /  72 -> 106 /  66
+//    8 experts x   83 rows, H 4096, F 14336:  386 / 284 -> 347 / 169
+//   64 experts x   16 rows, H 2048, F 768:     93 /  50 ->  70 /  42
+// (phase 2 storing bf16 rows).  A copy without the MFMAs takes 572 instead of 625 us in the first
+// line and the same 107 in the fourth: the loads bound the kernel throughout.
 // The weights of an item of up to 64 rows are loaded non-temporally (118 -> 108 us for
 // phase 1 at 40 rows a group, 79 -> 72 at 16; phase 2 63 -> 66 and 51 -> 42): they are read
 // once.  With more rows it gained nothing (128 -> 122 and 69 -> 80 us at 100 rows).
+//
+// The gathered rows, the activations and the expert outputs are stored non-temporally: the next
+// launch reads them, from other XCDs, and here they would push the panels out of the L2
+// (layer calls: 333 tokens x 8 wide experts 549 -> 540 us, 8192 tokens 1243 -> 1227).
 //
 // Items come from tables that the token gather writes.  Workgroups start on items
 // 0, 1, ... and claim further ones from a counter per XCD (the hardware deals workgroups
@@ -937,7 +943,7 @@ __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int parts, int bl
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int idx = base + 256 * u + threadIdx.x;
-            if (idx < i1) dst[idx] = v[u];
+            if (idx < i1) __builtin_nontemporal_store(v[u], dst + idx);
         }
     }
 }
@@ -1187,7 +1193,8 @@ __global__ void __launch_bounds__(256, 2)
             for (int c = tid; c < nblk * 2 * 64; c += 256) {
                 const int blk = c >> 6, piece = c & 63;
                 const u32x4 v = *reinterpret_cast<const u32x4*>(sbuf + blk * 1024 + 16 * piece);
-                *reinterpret_cast<u32x4*>(act + ((size_t)(blk >> 1) * (a.Fa / 32) + (blk & 1)) * 512 + 8 * piece) = v;
+                __builtin_nontemporal_store(
+                    v, reinterpret_cast<u32x4*>(act + ((size_t)(blk >> 1) * (a.Fa / 32) + (blk & 1)) * 512 + 8 * piece));
             }
         } else {
             // the group's rows x 16 pieces of 8 outputs, those that exist: bf16 rows for the
@@ -1201,7 +1208,7 @@ __global__ void __launch_bounds__(256, 2)
                 const u32x4 v = *reinterpret_cast<const u32x4*>(sbuf + (nl * kTPitch + 8 * piece) * 2);
                 const size_t to = at + (size_t)nl * a.H + 8 * piece;
                 if (a.y16) {
-                    *reinterpret_cast<u32x4*>(a.y16 + to) = v;
+                    __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(a.y16 + to));
                 } else {
                     *reinterpret_cast<f32x4*>(a.y + to) = bf16x4_to_f32(u32x2{v.x, v.y});
                     *reinterpret_cast<f32x4*>(a.y + to + 4) = bf16x4_to_f32(u32x2{v.z, v.w});
