@@ -599,7 +599,7 @@ def measure_workload(name, cfg, args, steps: int, warmup: int, cpu_seconds: floa
         achieved = alg["phase1_flops"] / p1_s / 1e12
         peak = mfma_peak_tflops(cfg.dtype)
         kname = ("k_ffn_tiled (phase 1: gate/up projections + SwiGLU)" if cfg.dtype == "bf16" else
-                 "k_ffn_stream fp32, 64-row chunks (phase 1: gate/up projections + SwiGLU)")
+                 "k_ffn_tiled_f32 (phase 1: gate/up projections + SwiGLU)")
         roofline = {"kernel": kname, "bound": "mfma",
                     "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                     "frac": achieved / peak, "traffic": traffic,
