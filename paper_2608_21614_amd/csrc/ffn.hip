@@ -762,6 +762,11 @@ __host__ __device__ constexpr int weight_tiles(int H, int Fg, bool down) {
     return down ? (H + kTR - 1) / kTR : (Fg + kTF - 1) / kTF;
 }
 
+// Groups of the active list that the tables, the gathered rows and the activations have room
+// for.  Only experts that share a slot, which the interface forbids but promises to survive,
+// make the list longer; the ones past it are not run.
+__device__ __forceinline__ int runnable(const Args& a, int nact) { return min(nact, a.max_routed); }
+
 // The groups of the tiled kernels -- the S shared experts and the active resident routed
 // ones, with their (segment start, count, slot) in s_info -- in order of falling row count,
 // so that the long items start first: s_ord[o] = group, s_rows[group] = its rows (group gi:
@@ -894,7 +899,7 @@ __global__ void __launch_bounds__(256) k_gather_tokens(Args a, int parts, int bl
         pack_offloaded(a, wg - blocks_max * split, gridDim.x - parts - blocks_max * split, 2);
         return;
     }
-    const int nact = list_active(a, s_list, s_wsum, s_info);
+    const int nact = runnable(a, list_active(a, s_list, s_wsum, s_info));
     const int rb_routed =
         group_prefix(nact, s_bpre, s_wsum + 4, [&](int gi) { return (max(s_info[gi].y, 0) + 15) / 16; });
     if (wg < 0) {
@@ -1278,7 +1283,7 @@ __global__ void __launch_bounds__(256) k_tile_groups(Args a) {
         pack_offloaded(a, blockIdx.x - 1, gridDim.x - 1, 4);
         return;
     }
-    const int nact = list_active(a, s_list, s_wsum, s_info);
+    const int nact = runnable(a, list_active(a, s_list, s_wsum, s_info));
     const int ng = nact + a.S;
     order_groups(a, nact, s_info, s_rows, s_ord);
     TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);

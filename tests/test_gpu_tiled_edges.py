@@ -4,9 +4,12 @@ and 128 rows), more token tiles than one sweep takes, a single K slab pair, widt
 leave half a weight tile, and more groups and items than workgroups start with."""
 from __future__ import annotations
 
+import numpy as np
 import pytest
 import torch
 
+import oracle
+from gpu_support import TOL, host_f64, rel_l2
 from test_gpu_parity import run_and_check_layer
 from workloads import make_layer
 
@@ -42,3 +45,42 @@ def test_tile_edges(moe, dtype, T, H, E, F, k, S, Fs, res):
     lay = make_layer(T, H, E, F, k, dtype=dtype, shared=S, shared_ffn=Fs, n_resident=res, residency="random",
                      bias="zipf", seed=T + H)
     run_and_check_layer(moe, lay)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T,E,k,S,slots", [(70, 12, 3, 2, 5), (150, 64, 8, 0, 3)])
+def test_shared_slots_stay_in_their_room(moe, dtype, T, E, k, S, slots):
+    """Resident experts that share slots (more of them than slots): the experts that the tables
+    have room for run as any others, the rows of the rest are left alone, and nothing is
+    written past the workspace."""
+    from paper_2608_21614_amd.device import DeviceLayer, to_device, to_host
+    print(f"[case] shared slots {dtype} T={T} E={E} k={k} S={S} slots={slots}", flush=True)
+    H, F, Fs = 192, 128, 64
+    lay = make_layer(T, H, E, F, k, dtype=dtype, shared=S, shared_ffn=Fs if S else 0, n_resident=slots, residency="random",
+                     bias="none", seed=T + E)
+    holds = lay.slot_experts()                       # slot -> the expert whose weights are in it
+    dev = DeviceLayer(lay)
+    dev.set_residency(np.arange(E) % slots)
+    o = dev.alloc_outputs()
+    n = moe.moe_workspace_bytes(dev.dims)
+    ws = torch.full((n + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    moe.moe_layer_forward(dev.args(o), ws[:n])       # the fused call returns, too
+    y = torch.full((T * k + S * T, H), 777.0, dtype=torch.float32, device="cuda")
+    moe.moe_grouped_ffn(dev.dims, dev.x, o["perm"], o["counts"], o["seg_start"], dev.expert_slot, dev.w13, dev.w2,
+                        dev.ws13, dev.ws2, y, ws[:n])
+    torch.cuda.synchronize()
+    assert bool((ws[n:] == 0xA5).all())
+    counts, seg, perm, got = to_host(o["counts"]), to_host(o["seg_start"]), to_host(o["perm"]), host_f64(y)
+    active = np.flatnonzero(counts)
+    assert len(active) > slots
+    for i, e in enumerate(active):
+        rows = slice(seg[e], seg[e] + counts[e])
+        if i < slots:
+            w = int(holds[e % slots])
+            ref = oracle.expert_ffn(lay.x, (perm[rows] // k).astype(np.int32), lay.w13(w), lay.w2(w))
+            assert rel_l2(got[rows], ref) <= TOL[dtype], e
+        else:
+            assert (got[rows] == 777.0).all(), e
+    for s in range(S):
+        ref = oracle.expert_ffn(lay.x, np.arange(T, dtype=np.int32), lay.ws13(s), lay.ws2(s))
+        assert rel_l2(got[T * k + s * T:T * k + (s + 1) * T], ref) <= TOL[dtype]
