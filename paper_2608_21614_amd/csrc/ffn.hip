@@ -1306,6 +1306,7 @@ __global__ void __launch_bounds__(256, 2)
     k_ffn_tiled_f32(Args a, const TileGroup* __restrict__ groups, const int32_t* __restrict__ pre, int32_t* claim) {
     __shared__ __attribute__((aligned(1024))) uint8_t sbuf[kFLds];
     __shared__ int32_t s_next;
+    __shared__ uint8_t s_live[kFN];  // phase 1: the item's row names a token of the batch
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave & 1, wn = wave >> 1;
@@ -1368,7 +1369,8 @@ __global__ void __launch_bounds__(256, 2)
             constexpr int S = NB <= 4 ? 3 : 2;    // stages of the ring
             static_assert(S * kSlab <= kFLds, "ring");
             // token row of this lane in load i: row 8 (j % 2) + lane / 8 of token block j / 2,
-            // j = wave LX + i; rows past the group read the item's first row (never stored)
+            // j = wave LX + i; rows past the group read the item's first row (never stored), and
+            // rows that name no token read the batch's first (zeros are stored in their place)
             const float* gx[LX];
 #pragma unroll
             for (int i = 0; i < LX; ++i) {
@@ -1381,9 +1383,11 @@ __global__ void __launch_bounds__(256, 2)
                     int t = nn;
                     if (!shared) {
                         const int q = a.perm[tg.rowbase + nn];
-                        t = q >= 0 ? q / a.k : 0;
-                        t = t < a.T ? t : 0;
+                        t = q >= 0 ? q / a.k : -1;
+                        t = t < a.T ? t : -1;
                     }
+                    if ((lane & 7) == 0) s_live[n] = t >= 0;
+                    t = max(t, 0);
                     row = (size_t)t * a.H;
                 }
                 gx[i] = static_cast<const float*>(kDown ? a.act : a.x) + row + 4 * ((lane & 7) ^ (lane >> 3));
@@ -1474,11 +1478,12 @@ __global__ void __launch_bounds__(256, 2)
                 if (!kDown) {
                     float* dst = static_cast<float*>(a.act) + (size_t)(tg.rowbase + n0 + nl) * a.Fa + r0 + 32 * wm +
                                  4 * (lane >> 4);
+                    const bool live = s_live[nl];
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
                         const f32x4 gv = tot[n][m], uv = tot[n][m + 2];
-                        *reinterpret_cast<f32x4*>(dst + 16 * m) = f32x4{silu(gv.x) * uv.x, silu(gv.y) * uv.y,
-                                                                       silu(gv.z) * uv.z, silu(gv.w) * uv.w};
+                        const f32x4 v = {silu(gv.x) * uv.x, silu(gv.y) * uv.y, silu(gv.z) * uv.z, silu(gv.w) * uv.w};
+                        *reinterpret_cast<f32x4*>(dst + 16 * m) = live ? v : f32x4{0.f, 0.f, 0.f, 0.f};
                     }
                 } else {
                     const int h = r0 + 64 * wm + 4 * (lane >> 4);

@@ -84,3 +84,28 @@ def test_shared_slots_stay_in_their_room(moe, dtype, T, E, k, S, slots):
     for s in range(S):
         ref = oracle.expert_ffn(lay.x, np.arange(T, dtype=np.int32), lay.ws13(s), lay.ws2(s))
         assert rel_l2(got[T * k + s * T:T * k + (s + 1) * T], ref) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,T", [("bf16", 40), ("bf16", 70), ("f32", 40), ("f32", 70), ("f32", 300)])
+def test_rows_without_a_pair_are_zero(moe, dtype, T):
+    """moe_grouped_ffn on its own, with packed rows that name no pair (-1, or past the batch) among
+    the resident ones: such a row has no token and its output is zero; the others are what they are
+    without it."""
+    from paper_2608_21614_amd.device import DeviceLayer, to_device, to_host
+    print(f"[case] rows without a pair {dtype} T={T}", flush=True)
+    lay = make_layer(T, 128, 4, 192, 2, dtype=dtype, shared=1, shared_ffn=64, n_resident=3, residency="random", seed=T)
+    dev = DeviceLayer(lay)
+    o = dev.alloc_outputs()
+    dev.forward(o)
+    P, n_res = 2 * T, int(to_host(o["n_res"])[0])
+    perm = to_host(o["perm"]).copy()
+    gone = np.arange(0, n_res, 5)
+    perm[gone] = np.resize([-1, P, -7, 2**30], len(gone))
+    y = [torch.full((P + T, 128), 777.0, dtype=torch.float32, device="cuda") for _ in range(2)]
+    for out, p in zip(y, (o["perm"], to_device(perm))):
+        moe.moe_grouped_ffn(dev.dims, dev.x, p, o["counts"], o["seg_start"], dev.expert_slot, dev.w13, dev.w2, dev.ws13,
+                            dev.ws2, out, dev.ws)
+    torch.cuda.synchronize()
+    want, got = to_host(y[0]).copy(), to_host(y[1])
+    want[gone] = 0.0
+    np.testing.assert_array_equal(got, want)
