@@ -15,11 +15,14 @@
 namespace saem {
 namespace {
 
-// One thread moves 8 consecutive K elements of one row in each of two neighbouring blocks (elt =
-// 2 or 4 bytes), so that a wave reads whole 128-byte lines of the rows; the stores, whose
-// lines nothing reads soon, are non-temporal.  HBM bounds it: one expert of H 4096, F 14336
-// (352 MB read, 352 MB written) took 128.6 us with half lines and plain stores, 122.3 with
-// non-temporal stores, 121.3 with both; non-temporal loads as well: 131.
+// A wave moves two neighbouring 16 x 32 blocks (elt = 2 or 4 bytes), so that it reads whole
+// 128-byte lines of the rows; lane l stores pieces l, l + 64, ... of 16 bytes of a block, so that
+// every store instruction of the wave writes 1 KB in one run, and past the caches, since nothing
+// reads the lines soon.  HBM bounds it: one expert of H 4096, F 14336 (as much written as read),
+//   bf16, 2 x 352 MB: half lines read and plain stores 127.5 us, non-temporal stores 122.3,
+//     with whole lines 120; non-temporal loads as well 131;
+//   fp32, 2 x 705 MB: 8 elements a lane with plain stores 255, non-temporal ones (half a line
+//     each) 520, one run per store 231.
 template <typename T>
 __global__ void __launch_bounds__(256)
     k_pack(const T* __restrict__ src, T* __restrict__ dst, long long rows, long long K) {
@@ -30,18 +33,21 @@ __global__ void __launch_bounds__(256)
         const long long p = c / 64, l = c % 64;
         const long long rt = p / pairs, s = 2 * (p % pairs);
         const bool two = s + 1 < nsteps;
-        const u32x4* in = reinterpret_cast<const u32x4*>(src + (16 * rt + (l & 15)) * K + 32 * s + 8 * (l >> 4));
-        u32x4* out = reinterpret_cast<u32x4*>(dst + (rt * nsteps + s) * 512 + l * 8);
         u32x4 v[2][kV];
+        u32x4* out = reinterpret_cast<u32x4*>(dst + (rt * nsteps + s) * 512) + l;
 #pragma unroll
         for (int i = 0; i < kV; ++i) {
-            v[0][i] = in[i];
-            if (two) v[1][i] = in[4 * kV + i];
+            // piece j of a block: part j % kV of the 8 elements that an MFMA reads with lane j / kV
+            const int j = (int)l + 64 * i, r = j / kV;
+            const u32x4* in =
+                reinterpret_cast<const u32x4*>(src + (16 * rt + (r & 15)) * K + 32 * s + 8 * (r >> 4)) + j % kV;
+            v[0][i] = in[0];
+            if (two) v[1][i] = in[4 * kV];
         }
 #pragma unroll
         for (int i = 0; i < kV; ++i) {
-            __builtin_nontemporal_store(v[0][i], out + i);
-            if (two) __builtin_nontemporal_store(v[1][i], out + 64 * kV + i);
+            __builtin_nontemporal_store(v[0][i], out + 64 * i);
+            if (two) __builtin_nontemporal_store(v[1][i], out + 64 * kV + 64 * i);
         }
     }
 }
