@@ -41,6 +41,7 @@
 // Both read counts and offsets from device memory: the stream kernel's grid is
 // sized for the worst case on the host and surplus workgroups exit at once; the
 // tiled kernel runs two workgroups per CU.
+#include <algorithm>
 #include <type_traits>
 
 #include "block_ops.hpp"
@@ -80,6 +81,7 @@ struct Args {
     void* xg;         // bf16 prefill: gathered token rows in the tile layout
     int32_t* tmeta;   // prefill: tables of the tiled kernels
     int tcap1;        // capacity of the phase-1 table
+    int cus;          // prefill: CUs of the device
     int32_t* tclaim;  // prefill: claim counters of the tiled kernels, eight per phase
     uint16_t* y16;    // bf16 prefill: expert outputs [rows][H] in bf16; null: the same values in y
     // decode with the repacking in phase 1 (fused): the ids, and the repack's outputs
@@ -695,7 +697,12 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
 // to the 8 XCDs round-robin), then from the other XCDs' once theirs is used up, so that
 // items of unequal length even out.  An XCD takes chunks of kTChunk neighbouring items,
 // which share weight and token panels in its L2.  Which workgroup runs an item does not
-// change its result.
+// change its result.  Up to one item per CU are dealt out evenly and without claims: in chunks
+// of 32, 192 items left two XCDs idle and others with items to be claimed late (phase 1 /
+// phase 2 in us; 4000 tokens, 16 experts, k 4, H 192, F 192: 23.6 / 26.5 -> 15.6 / 16.1; 5774
+// tokens, 4 experts + 2 shared, H 128, F 64: 23.2 / 23.4 -> 14.6 / 15.0).  An XCD's run is
+// then its share of neighbouring items; for fp32 eight items in turn, since a run that is one
+// whole expert was slower there (16 experts of H 3072, F 1024, 43 rows each: 75 against 55 us).
 
 constexpr int kTR = 128;           // weight rows per item
 constexpr int kTF = kTR / 2;       // features per item in phase 1
@@ -958,6 +965,12 @@ __device__ __forceinline__ int claimed_item(int q, int x) {
     return ((q / kTChunk) * 8 + x) * kTChunk + q % kTChunk;
 }
 
+// At most one item per CU: no claims.  The q-th workgroup of XCD x takes this item; the XCDs get
+// equal runs of neighbouring items (run: their length), or with run 0 eight items in turn.
+__device__ __forceinline__ int few_item(int q, int x, int run) {
+    return run == 0 ? ((q / 8) * 8 + x) * 8 + q % 8 : (q < run ? x * run + q : INT_MAX);
+}
+
 // The next item of XCD queue *xcd, or of another queue (then *xcd) once that one is empty;
 // -1 when all are.  By one wave; the counters only grow, so the loop ends.
 __device__ int next_item(int32_t* claim, int q0, int n_items, int* xcd) {
@@ -993,7 +1006,9 @@ __global__ void __launch_bounds__(256, 2)
     const int n_items = a.tmeta[kDown ? 1 : 0];
     const int q0 = gridDim.x / 8;  // claims up to here are the workgroups' first items
     int xcd = blockIdx.x % 8;
-    int item = claimed_item(blockIdx.x / 8, xcd);
+    const bool few = n_items <= a.cus;
+    int item = few ? few_item(blockIdx.x / 8, xcd, (n_items + 7) / 8) : claimed_item(blockIdx.x / 8, xcd);
+    if (few && item >= n_items) return;
 
     if (item >= n_items) {
         if (wave == 0) {
@@ -1129,7 +1144,7 @@ __global__ void __launch_bounds__(256, 2)
             }
             // claim the next item while the last slabs run (their waits cover the atomic)
             int got = 0;
-            if (wave == 0 && lane == 0)
+            if (!few && wave == 0 && lane == 0)
                 got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll 1
             for (; kt < nk; kt += 2) {
@@ -1150,7 +1165,8 @@ __global__ void __launch_bounds__(256, 2)
             __syncthreads();  // every wave is done with the last stage
             if (wave == 0) {
                 int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
-                if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
+                if (few) it = -1;
+                else if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
                 if (lane == 0) *s_next = it;
             }
             int elane = lane;  // opaque: the addresses below are not worth registers in the K loop
@@ -1315,7 +1331,9 @@ __global__ void __launch_bounds__(256, 2)
     const int n_items = a.tmeta[kDown ? 1 : 0], ng = a.tmeta[2];
     const int q0 = gridDim.x / 8;
     int xcd = blockIdx.x % 8;
-    int item = claimed_item(blockIdx.x / 8, xcd);
+    const bool few = n_items <= a.cus;
+    int item = few ? few_item(blockIdx.x / 8, xcd, 0) : claimed_item(blockIdx.x / 8, xcd);
+    if (few && item >= n_items) return;
     if (item >= n_items) {
         if (wave == 0) {
             const int it = next_item(claim, q0, n_items, &xcd);
@@ -1424,7 +1442,7 @@ __global__ void __launch_bounds__(256, 2)
                 __builtin_amdgcn_sched_barrier(0);
                 if (kt + S - 1 < nk) issue(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
                 // claim the next item while the last slabs run
-                if (kt == nk - 2 && wave == 0 && lane == 0)
+                if (!few && kt == nk - 2 && wave == 0 && lane == 0)
                     got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 const int so = stage * kSlab;
                 f32x4 A[2][4], B[2][NF];
@@ -1467,7 +1485,8 @@ __global__ void __launch_bounds__(256, 2)
             }
             if (wave == 0) {
                 int it = claimed_item(q0 + __builtin_amdgcn_readfirstlane(got), xcd);
-                if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
+                if (few) it = -1;
+                else if (it >= n_items) it = next_item(claim, q0, n_items, &xcd);
                 if (lane == 0) s_next = it;
             }
             // lane holds token lane % 16 of each 16 x 16 tile, weight rows 4 (lane / 16) .. + 3
@@ -1613,6 +1632,7 @@ Args make_args(const Shape& s, const FfnArgs& fa) {
     a.off_w = fa.off_w;
     a.xg = fa.xg;
     a.tmeta = fa.tmeta;
+    a.cus = 0;
     a.tclaim = fa.tclaim;
     a.tcap1 = tiled_bf16(s) ? (int)tiled_items(s, false) : 0;
     a.y16 = static_cast<uint16_t*>(fa.y16);
@@ -1651,6 +1671,15 @@ size_t ffn_tile_meta_bytes(const Shape& s) {
 }
 
 size_t ffn_tile_claim_bytes(const Shape& s) { return use_tiled(s) ? 2 * 8 * kTClaimPitch * sizeof(int32_t) : 0; }
+
+// CUs of the current device, the same number on each of its eight XCDs.
+static hipError_t device_cus(int* cus) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) *cus = std::max(*cus / 8 * 8, 8);
+    return e;
+}
 
 hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
@@ -1734,16 +1763,14 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
     }
     // tiled: two workgroups per CU, each claiming items from the tables written before; the
     // offloaded rows were packed there
-    int dev = 0, cus = 0;
-    if (hipError_t e = hipGetDevice(&dev); e != hipSuccess) return e;
-    if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev); e != hipSuccess)
-        return e;
-    const long long wgs = cus < 8 ? 8 : cus / 8 * 16;
+    if (hipError_t e = device_cus(&a.cus); e != hipSuccess) return e;
+    const long long wgs = 2 * a.cus;
     const TileGroup* groups = reinterpret_cast<const TileGroup*>(a.tmeta + kTHeader);
     const long long n_groups = a.max_routed + a.S;
     for (int down = 0; down < 2; ++down) {
         const long long items = tiled_items(s, down == 1);
-        const unsigned grid = (unsigned)(items < wgs ? (items + 7) / 8 * 8 : wgs);
+        // a workgroup per CU at least, so that as many items all start at once
+        const unsigned grid = items == 0 ? 0 : (unsigned)std::min(wgs, std::max<long long>(a.cus, (items + 7) / 8 * 8));
         int32_t* claim = a.tclaim + down * 8 * kTClaimPitch;
         if (grid > 0 && s.bf16) {
             const TileItem* tab = reinterpret_cast<const TileItem*>(groups + n_groups) + (down ? a.tcap1 : 0);

@@ -196,7 +196,34 @@ static void run(const Case& c) {
     }
 }
 
+// The persistent FFN kernels take every item once, from the claim queues and without them.
+static void check_queues() {
+    for (int n = 1; n <= 3000; n += n < 600 ? 1 : 7) {
+        std::vector<int> hit(n, 0);
+        for (int x = 0; x < 8; ++x)
+            for (int q = 0;; ++q) {
+                const int it = claimed_item(q, x);
+                if (it >= n) break;  // and so are all that follow in the queue
+                CHECK(it >= 0 && hit[it]++ == 0 && claimed_item(q + 1, x) > it, "%d of %d items", it, n);
+            }
+        CHECK(std::count(hit.begin(), hit.end(), 1) == n, "%d items", n);
+        const int cus = 256;
+        for (int run : {0, (n + 7) / 8}) {
+            if (n > cus) break;
+            std::fill(hit.begin(), hit.end(), 0);
+            int per_xcd[8] = {};
+            for (int wg = 0; wg < cus; ++wg) {
+                const int it = few_item(wg / 8, wg % 8, run);
+                if (it < n) ++hit[it], ++per_xcd[wg % 8];
+            }
+            CHECK(std::count(hit.begin(), hit.end(), 1) == n, "%d items, one per CU", n);
+            CHECK(*std::max_element(per_xcd, per_xcd + 8) <= (n / 64 + 1) * 8, "%d items spread unevenly", n);
+        }
+    }
+}
+
 int main() {
+    check_queues();
     // T, H, E, F, k, S, Fs, slots, bf16; resident, dropped
     std::vector<Case> cases;
     for (int bf16 = 0; bf16 < 2; ++bf16) {
