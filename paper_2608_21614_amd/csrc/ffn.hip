@@ -764,9 +764,10 @@ __device__ __forceinline__ void mfma_tied(f32x4& acc, bf16x8 a, bf16x8 b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
 
-// Weight tiles of a group of width Fg: phase 1 covers 64 features per tile, phase 2 128 rows of W2.
-__host__ __device__ constexpr int weight_tiles(int H, int Fg, bool down) {
-    return down ? (H + kTR - 1) / kTR : (Fg + kTF - 1) / kTF;
+// Weight tiles of a group of width Fg: rows of W2 in phase 2, in phase 1 half as many features
+// (their gate and up rows).
+__host__ __device__ constexpr int weight_tiles(int H, int Fg, bool down, int rows = kTR) {
+    return down ? (H + rows - 1) / rows : (Fg + rows / 2 - 1) / (rows / 2);
 }
 
 // Groups of the active list that the tables, the gathered rows and the activations have room
@@ -1245,8 +1246,8 @@ __global__ void __launch_bounds__(256, 2)
 // tiled kernel, fp32 prefill
 // ---------------------------------------------------------------------------
 //
-// The same items (128 weight rows x up to 128 of a group's rows) and claim queues on
-// v_mfma_f32_16x16x4_f32.  fp32 has a sixteenth of the bf16 MFMA rate, so the MFMAs bound
+// The same kind of items (128 weight rows x up to 128 of a group's rows, or smaller) and claim
+// queues on v_mfma_f32_16x16x4_f32.  fp32 has a sixteenth of the bf16 MFMA rate, so the MFMAs bound
 // it and its operands need no gathered copy: a 32-wide K slab of a row-major token row is a
 // whole 128-byte line, loaded straight into the LDS (eight lanes a row).  LDS images, both
 // read without bank conflicts:
@@ -1268,9 +1269,23 @@ __global__ void __launch_bounds__(256, 2)
 // Token tiles of 64 or 96 rows instead of 128: 1693 / 871 and 1674 / 857 at 256 rows.  What is
 // left: the last round of items (2816 for 512 workgroups in the first line) and the fragment
 // reads behind each barrier.
+//
+// Item shapes.  A CU multiplies a slab of 128 x 128 for 2 us, so a phase of few such items takes as
+// long as one of them, with most CUs idle; smaller items share it out.  The sums are the same in
+// every shape.  64 x 32 takes two slabs per stage, since a slab's MFMAs (0.2 us) are short against
+// a barrier.  Phase 1 / phase 2 in us, the stream kernel, 128 x 128 alone, and as chosen now:
+//    1 expert  x 257 rows, H 2048, F 1024:    45 / 27,   145 /  77,   45 / 26
+//    8 experts x  12 rows, H 2048, F 1024:    46 / 28,    54 /  32,   34 / 21
+//    4 experts x  75 rows, H 1024, F 4096:   113 / 79,    65 / 215,   63 / 54
+//    2 experts x  18 rows, H 4096, F 4096:    88 / 83,   102 /  97,   62 / 56
+//   64 experts x  64 rows, H  512, F  256:    62 / 38,    38 /  24,   39 / 24
 
-constexpr int kFN = 128;    // group rows per item
+constexpr int kFN = 128;    // largest number of group rows per item
 constexpr int kFLds = 72 * 1024;  // the ring of a workgroup: two workgroups per CU
+// Item shapes: 128 weight rows x 128 or 32 group rows, and 64 x 32.
+constexpr int kFShapes = 3;
+__host__ __device__ constexpr int shape_rows(int shape) { return shape == 0 ? kFN : 32; }
+__host__ __device__ constexpr int shape_weights(int shape) { return shape < 2 ? kTR : kTR / 2; }
 constexpr int kFFlush = 8;  // slabs between two additions into the second accumulators
 
 __device__ __forceinline__ void mfma_tied_f32(f32x4& acc, float a, float b) {
@@ -1285,9 +1300,52 @@ __device__ __forceinline__ void lds_load_1k_lanes(uint32_t lds, const void* p) {
                  : "memory", "m0");
 }
 
+// The item shape of a phase: the first whose longest item is at most so many times a CU's share of
+// the phase's work, else the last.  Times at a longest item of so many shares, 128 x 128, 128 x 32
+// and 64 x 32 in us:
+//   1.1: 152, 163, 180 (16 experts, H 2048, F 128, phase 1);   1.3: 67, 70, 80 (4 experts x 75
+//   rows, H 1024, phase 1) and 245, 263, 279 (8 x 83, H 4096, phase 2);   1.6: 40, 47, 47 (64 x 64,
+//   H 512);   1.9: 79, 69, 69 (4 x 179, H 1024);   2.2: 116, 68, 74;   above that 128 x 128 loses more;
+// and of the second shape's longest item, 128 x 32 and 64 x 32:
+//   0.8: 20, 21;   1.0: 25, 31 and 78, 73;   1.1: 21, 22;   1.3: 52, 51 and 38, 35;   1.6: 36, 24.
+// By every thread of the workgroup; s_red: 4 kFShapes floats.
+__device__ int item_shape(const Args& a, int ng, const int* s_rows, bool down, float* s_red) {
+    constexpr float kShare[kFShapes - 1] = {1.6f, 1.2f};
+    constexpr int N = kFShapes;
+    float v[N] = {};  // work, and each shape's longest item per weight row
+    for (int gi = threadIdx.x; gi < ng; gi += 256) {
+        const int Fg = gi < a.S ? a.Fs : a.F;
+        const float K = down ? Fg : a.H, w = down ? a.H : 2 * Fg;
+        const int rows = (s_rows[gi] + 31) / 32 * 32;
+        v[0] += K * w * rows;
+#pragma unroll
+        for (int i = 0; i < kFShapes - 1; ++i) v[1 + i] = fmaxf(v[1 + i], K * min(rows, shape_rows(i)));
+    }
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float o = __shfl_xor(v[i], off, kWave);
+            v[i] = i == 0 ? v[i] + o : fmaxf(v[i], o);
+        }
+    if (lane_id() == 0)
+#pragma unroll
+        for (int i = 0; i < N; ++i) s_red[N * (threadIdx.x >> 6) + i] = v[i];
+    __syncthreads();
+    const float share = (s_red[0] + s_red[N] + s_red[2 * N] + s_red[3 * N]) / a.cus;
+    int shape = 0;
+    for (; shape < kFShapes - 1; ++shape) {
+        const int i = 1 + shape;
+        const float longest = fmaxf(fmaxf(s_red[i], s_red[N + i]), fmaxf(s_red[2 * N + i], s_red[3 * N + i]));
+        if (longest * shape_weights(shape) <= kShare[shape] * share) break;
+    }
+    return shape;
+}
+
 // fp32 prefill: the groups in order and the prefix of their items, in tmeta: int32 header[8]
-// (items of phase 1, of phase 2, groups), TileGroup[groups], first item[groups] of phase 1
-// and of phase 2.  One workgroup; the others pack the offloaded rows.
+// (items of phase 1, of phase 2, groups, item shape of phase 1, of phase 2), TileGroup[groups],
+// first item[groups] of phase 1 and of phase 2.  A workgroup for each phase (a chain of round
+// trips and scans); the others pack the offloaded rows.
 __global__ void __launch_bounds__(256) k_tile_groups(Args a) {
     __shared__ int s_list[256];
     __shared__ int4 s_info[256];
@@ -1295,26 +1353,29 @@ __global__ void __launch_bounds__(256) k_tile_groups(Args a) {
     __shared__ int s_ipre[kGMaxGroups + 1];
     __shared__ int s_rows[kGMaxGroups];
     __shared__ int16_t s_ord[kGMaxGroups];
-    if (blockIdx.x > 0) {
-        pack_offloaded(a, blockIdx.x - 1, gridDim.x - 1, 4);
+    __shared__ float s_red[4 * kFShapes];
+    if (blockIdx.x > 1) {
+        pack_offloaded(a, blockIdx.x - 2, gridDim.x - 2, 4);
         return;
     }
+    const int ph = blockIdx.x;
     const int nact = runnable(a, list_active(a, s_list, s_wsum, s_info));
     const int ng = nact + a.S;
     order_groups(a, nact, s_info, s_rows, s_ord);
     TileGroup* groups = reinterpret_cast<TileGroup*>(a.tmeta + kTHeader);
-    write_tile_groups(a, ng, s_info, s_rows, s_ord, nullptr, 0, groups);
-    int32_t* pre = reinterpret_cast<int32_t*>(groups + a.max_routed + a.S);
-    for (int ph = 0; ph < 2; ++ph) {
-        const int total = group_prefix(ng, s_ipre, s_wsum + 5 + ph, [&](int o) {
-            const int gi = s_ord[o];
-            return weight_tiles(a.H, gi < a.S ? a.Fs : a.F, ph == 1) * ((s_rows[gi] + kFN - 1) / kFN);
-        });
-        for (int o = threadIdx.x; o < ng; o += 256) pre[ph * (a.max_routed + a.S) + o] = s_ipre[o];
-        if (threadIdx.x == 0) a.tmeta[ph] = total;
-        __syncthreads();  // s_ipre is rewritten for the next phase
+    if (ph == 0) write_tile_groups(a, ng, s_info, s_rows, s_ord, nullptr, 0, groups);
+    const int shape = item_shape(a, ng, s_rows, ph == 1, s_red), tn = shape_rows(shape), wr = shape_weights(shape);
+    const int total = group_prefix(ng, s_ipre, s_wsum + 5, [&](int o) {
+        const int gi = s_ord[o];
+        return weight_tiles(a.H, gi < a.S ? a.Fs : a.F, ph == 1, wr) * ((s_rows[gi] + tn - 1) / tn);
+    });
+    int32_t* pre = reinterpret_cast<int32_t*>(groups + a.max_routed + a.S) + ph * (a.max_routed + a.S);
+    for (int o = threadIdx.x; o < ng; o += 256) pre[o] = s_ipre[o];
+    if (threadIdx.x == 0) {
+        a.tmeta[ph] = total;
+        a.tmeta[3 + ph] = shape;
+        if (ph == 0) a.tmeta[2] = ng;
     }
-    if (threadIdx.x == 0) a.tmeta[2] = ng;
 }
 
 template <bool kDown>
@@ -1329,6 +1390,7 @@ __global__ void __launch_bounds__(256, 2)
     const uint32_t lds0 = (uint32_t)(uintptr_t)(lds_u8*)sbuf;
     const uint32_t woff = 16 * (2 * (lane & 31) + (lane >> 5));  // a lane's bytes of a 1 KB weight chunk
     const int n_items = a.tmeta[kDown ? 1 : 0], ng = a.tmeta[2];
+    const int shape = a.tmeta[kDown ? 4 : 3], tn = shape_rows(shape), wr = shape_weights(shape);
     const int q0 = gridDim.x / 8;
     int xcd = blockIdx.x % 8;
     const bool few = n_items <= a.cus;
@@ -1351,135 +1413,154 @@ __global__ void __launch_bounds__(256, 2)
         const TileGroup tg = groups[go];
         const bool shared = tg.wsel < 0;
         const int Fg = shared ? a.Fs : a.F;
-        const int ntt = (tg.count + kFN - 1) / kFN;
+        const int ntt = (tg.count + tn - 1) / tn;
         int wt, tt;
-        item_tiles(item - pre[go], weight_tiles(a.H, Fg, kDown), ntt, &wt, &tt);
-        const int n0 = __builtin_amdgcn_readfirstlane(tt) * kFN;
-        const int r0 = __builtin_amdgcn_readfirstlane(wt) * (kDown ? kTR : kTF);
+        item_tiles(item - pre[go], weight_tiles(a.H, Fg, kDown, wr), ntt, &wt, &tt);
+        const int n0 = __builtin_amdgcn_readfirstlane(tt) * tn;
+        const int r0 = __builtin_amdgcn_readfirstlane(wt) * (kDown ? wr : wr / 2);
         const int K = kDown ? Fg : a.H;
         const int nk = K / 32;
         const size_t wsize = (size_t)(kDown ? 1 : 2) * Fg * a.H;
         const float* wbase = shared ? static_cast<const float*>(kDown ? a.ws2 : a.ws13) + (size_t)(-tg.wsel - 1) * wsize
                                     : static_cast<const float*>(kDown ? a.w2 : a.w13) + (size_t)tg.wsel * wsize;
-        // this wave loads LDS weight blocks 2 wave, 2 wave + 1; phase 1: gate rows in blocks
-        // 0..3, up rows in 4..7; a row tile past the matrix reads tile 0 (never stored)
+        // this wave's weight blocks (one if the item has four); phase 1: gate rows in the first half of
+        // the blocks, the same features' up rows in the second; a row tile past the matrix reads
+        // tile 0 (never stored)
         const float* gw[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int b = 2 * wave + i;
+            const int b = wr < kTR ? wave : 2 * wave + i;
             int rt;
             if (kDown) {
                 rt = r0 / 16 + b;
                 if (16 * rt >= a.H) rt = 0;
             } else {
-                rt = (b >> 2) * (Fg / 16) + r0 / 16 + (b & 3);
+                const int half = wr / 32;
+                rt = (b >= half ? Fg / 16 + b - half : b) + r0 / 16;
             }
             gw[i] = wbase + (size_t)rt * nk * 512;
         }
-        const int rows = min(kFN, tg.count - n0);
+        const int rows = min(tn, tg.count - n0);
 
-        // the item with its tokens in NB blocks (2, 4, 6 or 8)
-        auto run = [&](auto nb_tag) {
-            constexpr int NB = decltype(nb_tag)::value;
-            constexpr int NF = NB / 2;            // token fragments of a wave: blocks 2 n + wn
-            constexpr int LX = NB / 2, L = 4 + LX;  // loads of a wave per slab
-            constexpr int kSlab = (8 + NB) * 2048;
-            constexpr int S = NB <= 4 ? 3 : 2;    // stages of the ring
-            static_assert(S * kSlab <= kFLds, "ring");
+        // the item with its weight rows in WB blocks (4 or 8), its tokens in NB (2, 4, 6 or 8)
+        auto run = [&](auto wb_tag, auto nb_tag) {
+            constexpr int WB = decltype(wb_tag)::value, NB = decltype(nb_tag)::value;
+            constexpr int NW = WB / 2, NF = NB / 2;  // a wave's weight fragments, and its tokens': blocks 2 n + wn
+            constexpr int U = WB == 4 ? 2 : 1;              // slabs per stage and barrier (nk is even)
+            constexpr int LW = WB / 2, LX = NB / 2, L = U * (LW + LX);  // loads of a wave per slab, per stage
+            constexpr int kSlab = (WB + NB) * 2048, kTok = WB * 2048;
+            constexpr int S = NB <= 4 ? 3 : 2;              // stages of the ring
+            static_assert(S * U * kSlab <= kFLds && (S - 1) * L < 64, "ring");
+            const int ns = nk / U;
+            // this wave's first weight and token chunk of stage 0; opaque, so that the sums with them are
+            // made where they are used and not kept in registers across the items
+            uint32_t wring = lds0 + wave * LW * 1024, xring = lds0 + kTok + wave * LX * 1024;
+            asm volatile("" : "+s"(wring), "+s"(xring));
             // token row of this lane in load i: row 8 (j % 2) + lane / 8 of token block j / 2,
             // j = wave LX + i; rows past the group read the item's first row (never stored), and
             // rows that name no token read the batch's first (zeros are stored in their place)
             const float* gx[LX];
+            int tok[LX];  // the loads' rows, then their tokens
 #pragma unroll
             for (int i = 0; i < LX; ++i) {
                 const int n = 8 * (wave * LX + i) + (lane >> 3);
-                const int nn = n0 + (n < rows ? n : 0);
-                size_t row;
-                if (kDown) {
-                    row = (size_t)(tg.rowbase + nn) * a.Fa;
-                } else {
-                    int t = nn;
-                    if (!shared) {
-                        const int q = a.perm[tg.rowbase + nn];
-                        t = q >= 0 ? q / a.k : -1;
-                        t = t < a.T ? t : -1;
-                    }
-                    if ((lane & 7) == 0) s_live[n] = t >= 0;
-                    t = max(t, 0);
-                    row = (size_t)t * a.H;
-                }
-                gx[i] = static_cast<const float*>(kDown ? a.act : a.x) + row + 4 * ((lane & 7) ^ (lane >> 3));
+                tok[i] = n0 + (n < rows ? n : 0);
             }
-            auto issue = [&](int kt, int stage) {
-                const uint32_t to = lds0 + stage * kSlab;
+            if (!kDown) {
+                if (!shared) {
+                    // all of the loads before the first use
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    lds_load_1k<false>(to + (2 * wave + i / 2) * 2048 + (i % 2) * 1024,
-                                       gw[i / 2] + (size_t)kt * 512 + (i % 2) * 256, woff);
+                    for (int i = 0; i < LX; ++i) tok[i] = a.perm[tg.rowbase + tok[i]];
 #pragma unroll
-                for (int i = 0; i < LX; ++i)
-                    lds_load_1k_lanes(to + 16384 + (wave * LX + i) * 1024, gx[i] + (size_t)kt * 32);
+                    for (int i = 0; i < LX; ++i) {
+                        const int q = tok[i], t = max(q, 0) / a.k;
+                        tok[i] = q < 0 || t >= a.T ? -1 : t;
+                    }
+                }
+                if ((lane & 7) == 0)
+#pragma unroll
+                    for (int i = 0; i < LX; ++i) s_live[8 * (wave * LX + i) + (lane >> 3)] = tok[i] >= 0;
+            }
+#pragma unroll
+            for (int i = 0; i < LX; ++i)
+                gx[i] = static_cast<const float*>(kDown ? a.act : a.x) + 4 * ((lane & 7) ^ (lane >> 3)) +
+                        (kDown ? (size_t)(tg.rowbase + tok[i]) * a.Fa : (size_t)max(tok[i], 0) * a.H);
+            auto issue = [&](int st, int stage) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t to = (stage * U + u) * kSlab;
+                    const int kt = st * U + u;
+#pragma unroll
+                    for (int i = 0; i < LW; ++i)
+                        lds_load_1k<false>(wring + to + i * 1024, gw[i / 2] + (size_t)kt * 512 + (i % 2) * 256, woff);
+#pragma unroll
+                    for (int i = 0; i < LX; ++i) lds_load_1k_lanes(xring + to + i * 1024, gx[i] + (size_t)kt * 32);
+                }
             };
-            f32x4 acc[NF][4], tot[NF][4];
+            f32x4 acc[NF][NW], tot[NF][NW];
 #pragma unroll
             for (int n = 0; n < NF; ++n)
 #pragma unroll
-                for (int m = 0; m < 4; ++m) acc[n][m] = tot[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int m = 0; m < NW; ++m) acc[n][m] = tot[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int st = 0; st < S - 1; ++st)
-                if (st < nk) issue(st, st);
+                if (st < ns) issue(st, st);
             // this lane's first piece of a weight block, and of a token block's row lane % 16
             const uint8_t* aw = sbuf + (lane >> 5) * 1024 + (lane & 31) * 16;
-            const uint8_t* bx = sbuf + 16384 + (lane & 15) * 128;
+            const uint8_t* bx = sbuf + kTok + (lane & 15) * 128;
             const int p0 = 2 * (lane >> 4), sw = lane & 7;
             const int b_lo = ((p0 ^ sw) * 16), b_hi = (((p0 + 1) ^ sw) * 16);
             int stage = 0, got = 0;
 #pragma unroll 1
-            for (int kt = 0; kt < nk; ++kt) {
+            for (int st = 0; st < ns; ++st) {
                 __builtin_amdgcn_sched_barrier(0);
-                if (S > 2 && nk - 1 - kt >= S - 2) wait_then_barrier<(S - 2) * L>();
+                if (S > 2 && ns - 1 - st >= S - 2) wait_then_barrier<(S - 2) * L>();
                 else wait_then_barrier<0>();
                 __builtin_amdgcn_sched_barrier(0);
-                if (kt + S - 1 < nk) issue(kt + S - 1, stage == 0 ? S - 1 : stage - 1);
+                if (st + S - 1 < ns) issue(st + S - 1, stage == 0 ? S - 1 : stage - 1);
                 // claim the next item while the last slabs run
-                if (!few && kt == nk - 2 && wave == 0 && lane == 0)
+                if (!few && st == (U == 1 ? ns - 2 : ns - 1) && wave == 0 && lane == 0)
                     got = __hip_atomic_fetch_add(claim + xcd * kTClaimPitch, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int so = stage * kSlab;
-                f32x4 A[2][4], B[2][NF];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
+                for (int u = 0; u < U; ++u) {
+                    const int so = (stage * U + u) * kSlab, kt = st * U + u;
+                    f32x4 A[2][NW], B[2][NF];
 #pragma unroll
-                    for (int m = 0; m < 4; ++m) {
-                        const int blk = kDown ? 4 * wm + m : (m < 2 ? 2 * wm + m : 4 + 2 * wm + m - 2);
-                        A[h][m] = *reinterpret_cast<const f32x4*>(aw + so + blk * 2048 + h * 512);
+                    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                        for (int m = 0; m < NW; ++m) {
+                            constexpr int kHalf = NW / 2;  // phase 1: as many gate as up fragments
+                            const int blk = kDown ? NW * wm + m : m / kHalf * (WB / 2) + kHalf * wm + m % kHalf;
+                            A[h][m] = *reinterpret_cast<const f32x4*>(aw + so + blk * 2048 + h * 512);
+                        }
+#pragma unroll
+                        for (int n = 0; n < NF; ++n)
+                            B[h][n] = *reinterpret_cast<const f32x4*>(bx + so + (2 * n + wn) * 2048 + (h ? b_hi : b_lo));
                     }
+                    // K 8 (lane / 16) + 4 h + i of the slab, over all tiles before the next i
 #pragma unroll
-                    for (int n = 0; n < NF; ++n)
-                        B[h][n] = *reinterpret_cast<const f32x4*>(bx + so + (2 * n + wn) * 2048 + (h ? b_hi : b_lo));
-                }
-                // K 8 (lane / 16) + 4 h + i of the slab, over all tiles before the next i
+                    for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
+                        for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i)
+                            for (int n = 0; n < NF; ++n)
+#pragma unroll
+                                for (int m = 0; m < NW; ++m) mfma_tied_f32(acc[n][m], A[h][m][i], B[h][n][i]);
+                    if (u == U - 1 && (kt % kFFlush == kFFlush - 1 || kt == nk - 1)) {
+                        // the MFMAs' results are read as ordinary registers: cover their latency
+                        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int n = 0; n < NF; ++n)
 #pragma unroll
-                            for (int m = 0; m < 4; ++m) mfma_tied_f32(acc[n][m], A[h][m][i], B[h][n][i]);
-                if (kt % kFFlush == kFFlush - 1 || kt == nk - 1) {
-                    // the MFMAs' results are read as ordinary registers: cover their latency
-                    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int n = 0; n < NF; ++n)
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) {
-                            asm volatile("" : "+v"(acc[n][m]));
-                            tot[n][m] += acc[n][m];
-                            acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        }
-                    asm volatile("s_nop 7" ::: "memory");
-                    __builtin_amdgcn_sched_barrier(0);
+                            for (int m = 0; m < NW; ++m) {
+                                asm volatile("" : "+v"(acc[n][m]));
+                                tot[n][m] += acc[n][m];
+                                acc[n][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+                            }
+                        asm volatile("s_nop 7" ::: "memory");
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
                 stage = stage == S - 1 ? 0 : stage + 1;
             }
@@ -1495,29 +1576,32 @@ __global__ void __launch_bounds__(256, 2)
                 const int nl = 16 * (2 * n + wn) + (lane & 15);
                 if (nl >= rows) continue;
                 if (!kDown) {
-                    float* dst = static_cast<float*>(a.act) + (size_t)(tg.rowbase + n0 + nl) * a.Fa + r0 + 32 * wm +
+                    float* dst = static_cast<float*>(a.act) + (size_t)(tg.rowbase + n0 + nl) * a.Fa + r0 + 8 * NW * wm +
                                  4 * (lane >> 4);
                     const bool live = s_live[nl];
 #pragma unroll
-                    for (int m = 0; m < 2; ++m) {
-                        const f32x4 gv = tot[n][m], uv = tot[n][m + 2];
+                    for (int m = 0; m < NW / 2; ++m) {
+                        const f32x4 gv = tot[n][m], uv = tot[n][m + NW / 2];
                         const f32x4 v = {silu(gv.x) * uv.x, silu(gv.y) * uv.y, silu(gv.z) * uv.z, silu(gv.w) * uv.w};
                         *reinterpret_cast<f32x4*>(dst + 16 * m) = live ? v : f32x4{0.f, 0.f, 0.f, 0.f};
                     }
                 } else {
-                    const int h = r0 + 64 * wm + 4 * (lane >> 4);
+                    const int h = r0 + 16 * NW * wm + 4 * (lane >> 4);
                     float* dst = a.y + (size_t)(tg.rowbase + n0 + nl) * a.H + h;
 #pragma unroll
-                    for (int m = 0; m < 4; ++m)
+                    for (int m = 0; m < NW; ++m)
                         if (h + 16 * m < a.H) *reinterpret_cast<f32x4*>(dst + 16 * m) = tot[n][m];
                 }
             }
         };
         const int nb = (rows + 31) / 32;
-        if (nb <= 1) run(std::integral_constant<int, 2>{});
-        else if (nb == 2) run(std::integral_constant<int, 4>{});
-        else if (nb == 3) run(std::integral_constant<int, 6>{});
-        else run(std::integral_constant<int, 8>{});
+        using W4 = std::integral_constant<int, 4>;
+        using W8 = std::integral_constant<int, 8>;
+        if (wr < kTR) run(W4{}, std::integral_constant<int, 2>{});
+        else if (nb <= 1) run(W8{}, std::integral_constant<int, 2>{});
+        else if (nb == 2) run(W8{}, std::integral_constant<int, 4>{});
+        else if (nb == 3) run(W8{}, std::integral_constant<int, 6>{});
+        else run(W8{}, std::integral_constant<int, 8>{});
         __syncthreads();  // every wave is done with the ring
         item = __builtin_amdgcn_readfirstlane(s_next);
     }
@@ -1602,11 +1686,10 @@ long long tiled_t16(const Shape& s) { return (s.T + 15) / 16 * 16ll; }
 bool use_tiled(const Shape& s) { return !use_stream(s); }
 bool tiled_bf16(const Shape& s) { return s.bf16 && use_tiled(s); }
 
-// Worst-case items of a tiled phase for row tiles of `rows` weight rows (phase 1: half as
-// many features): the routed groups have at most ceil(P / tn) full token tiles of tn rows
-// plus one partial tile each
-long long tiled_items_of(const Shape& s, bool down, int rows) {
-    const int tn = s.bf16 ? kTN : kFN;
+// Worst-case items of a tiled phase for items of `rows` weight rows (phase 1: half as many
+// features) x tn group rows: the routed groups have at most ceil(P / tn) full token tiles plus
+// one partial tile each
+long long tiled_items_of(const Shape& s, bool down, int rows, int tn) {
     const long long P = (long long)s.T * s.k;
     const long long G = max_routed_groups(s);
     const long long rt = G == 0 ? 0 : (P + tn - 1) / tn + G;
@@ -1616,7 +1699,8 @@ long long tiled_items_of(const Shape& s, bool down, int rows) {
     const long long wt_r = (s.F + f - 1) / f, wt_s = s.S > 0 ? (s.Fs + f - 1) / f : 0;
     return rt * wt_r + (long long)s.S * tps * wt_s;
 }
-long long tiled_items(const Shape& s, bool down) { return tiled_items_of(s, down, kTR); }
+// Entries of a phase's table (bf16).
+long long tiled_items(const Shape& s, bool down) { return tiled_items_of(s, down, kTR, kTN); }
 
 Args make_args(const Shape& s, const FfnArgs& fa) {
     Args a;
@@ -1666,7 +1750,7 @@ size_t ffn_tile_meta_bytes(const Shape& s) {
     // the workspace of a shape is part of the interface (the fixed scratch array accepts or
     // refuses a layer by it): the tables keep the room that 32 bytes per 256-row tile take,
     // which is always enough
-    const size_t room = 32 + 32 * (size_t)(tiled_items_of(s, false, 256) + tiled_items_of(s, true, 256));
+    const size_t room = 32 + 32 * (size_t)(tiled_items_of(s, false, 256, kTN) + tiled_items_of(s, true, 256, kTN));
     return need > room ? need : room;
 }
 
@@ -1683,11 +1767,12 @@ static hipError_t device_cus(int* cus) {
 
 hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
-    const Args a = make_args(s, fa);
+    Args a = make_args(s, fa);
     const int P = s.T * s.k;
     const int n_pack = (fa.off_rows || fa.off_w) ? (P < 256 ? P : 256) : 0;
     if (!s.bf16) {
-        hipLaunchKernelGGL(k_tile_groups, dim3((unsigned)(1 + n_pack)), dim3(256), 0, st, a);
+        if (hipError_t e = device_cus(&a.cus); e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_tile_groups, dim3((unsigned)(2 + n_pack)), dim3(256), 0, st, a);
         return hipGetLastError();
     }
     const long long blocks = ffn_gather_rows(s) / 16;
@@ -1768,8 +1853,9 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
     const TileGroup* groups = reinterpret_cast<const TileGroup*>(a.tmeta + kTHeader);
     const long long n_groups = a.max_routed + a.S;
     for (int down = 0; down < 2; ++down) {
-        const long long items = tiled_items(s, down == 1);
         // a workgroup per CU at least, so that as many items all start at once
+        const long long items = s.bf16 ? tiled_items(s, down == 1)
+                                       : tiled_items_of(s, down == 1, shape_weights(kFShapes - 1), shape_rows(kFShapes - 1));
         const unsigned grid = items == 0 ? 0 : (unsigned)std::min(wgs, std::max<long long>(a.cus, (items + 7) / 8 * 8));
         int32_t* claim = a.tclaim + down * 8 * kTClaimPitch;
         if (grid > 0 && s.bf16) {

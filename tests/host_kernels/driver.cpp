@@ -33,6 +33,8 @@ static std::unique_ptr<T[]> filled(size_t n, T v) {
     return p;
 }
 
+static int shapes_seen[kFShapes];  // fp32: phases that took each item shape
+
 static void run(const Case& c) {
     const Shape& s = c.s;
     const int P = s.T * s.k, H = s.H;
@@ -123,7 +125,6 @@ static void run(const Case& c) {
     const TileGroup* groups = reinterpret_cast<const TileGroup*>(meta.get() + kTHeader);
     const TileItem* tab = reinterpret_cast<const TileItem*>(groups + max_groups);
     const int32_t* pre = reinterpret_cast<const int32_t*>(groups + max_groups);
-    const int tn = s.bf16 ? kTN : kFN;
     if (!s.bf16) CHECK(meta[2] == ng, "%d groups, not %d", meta[2], ng);
 
     // row blocks of the gathered copy and of the activations, in the active list's order
@@ -155,18 +156,22 @@ static void run(const Case& c) {
 
     // every weight tile of every group meets every token tile once, in either phase
     for (int ph = 0; ph < 2; ++ph) {
+        const int shape = s.bf16 ? 0 : meta[3 + ph];
+        CHECK(shape >= 0 && shape < kFShapes, "phase %d: shape %d", ph, shape);
+        const int tn = s.bf16 ? kTN : shape_rows(shape), wr = shape_weights(shape);
+        if (!s.bf16) ++shapes_seen[shape];
         std::vector<int> first(ng + 1, 0);
         for (int o = 0; o < ng; ++o)
-            first[o + 1] = first[o] + weight_tiles(H, group_fg[o], ph == 1) * ((group_rows[o] + tn - 1) / tn);
-        CHECK(meta[ph] == first[ng] && first[ng] <= tiled_items(s, ph == 1), "phase %d: %d items, not %d (room %lld)", ph,
-              meta[ph], first[ng], tiled_items(s, ph == 1));
+            first[o + 1] = first[o] + weight_tiles(H, group_fg[o], ph == 1, wr) * ((group_rows[o] + tn - 1) / tn);
+        CHECK(meta[ph] == first[ng], "phase %d: %d items, not %d", ph, meta[ph], first[ng]);
+        if (s.bf16) CHECK(first[ng] <= tiled_items(s, ph == 1), "phase %d: %d items", ph, first[ng]);
         if (!s.bf16) {
             for (int o = 0; o < ng; ++o) CHECK(pre[ph * max_groups + o] == first[o], "phase %d, group %d", ph, o);
             continue;
         }
         const TileItem* items = tab + (ph ? tiled_items(s, false) : 0);
         for (int o = 0; o < ng; ++o) {
-            const int nwt = weight_tiles(H, group_fg[o], ph == 1), ntt = (group_rows[o] + tn - 1) / tn;
+            const int nwt = weight_tiles(H, group_fg[o], ph == 1, wr), ntt = (group_rows[o] + tn - 1) / tn;
             std::vector<int> hit(nwt * ntt, 0);
             for (int i = first[o]; i < first[o + 1]; ++i) {
                 const int g = items[i].gt & 511, tt = items[i].gt >> 9, wt = items[i].wt;
@@ -253,7 +258,11 @@ int main() {
         c.dropped = pick(0, 3);
         cases.push_back(c);
     }
-    for (const Case& c : cases) run(c);
+    for (size_t i = 0; i < cases.size(); ++i) {
+        emu_cus = i % 4 == 0 ? 1 : (i % 4 == 1 ? 256 : 8);  // small cases take each item shape
+        run(cases[i]);
+    }
+    for (int i = 0; i < kFShapes; ++i) CHECK(shapes_seen[i] > 0, "item shape %d", i);
     printf("tables ok\n");
     return 0;
 }

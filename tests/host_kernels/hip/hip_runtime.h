@@ -44,7 +44,8 @@ typedef void* hipStream_t;
 typedef void* hipEvent_t;
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
-inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+inline int emu_cus = 256;  // the device's CUs
+inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = emu_cus, hipSuccess; }
 inline hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 
 using std::max;

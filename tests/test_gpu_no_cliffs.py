@@ -42,3 +42,19 @@ def test_pack_moves_fp32_as_fast_as_bf16(moe):
     bf16, f32 = times_us(*(lambda s=s, d=d: moe.moe_pack_weights(s, d) for s, d in zip(src, dst)))
     print(f"[cliff] pack: bf16 {bf16:.1f} us, fp32 {f32:.1f} us", flush=True)
     assert f32 <= 1.4 * bf16
+
+
+@pytest.mark.parametrize("H,E,F", [(2048, 1, 1024), (4096, 2, 256), (512, 2, 2048)])
+def test_fp32_past_the_decode_batch(moe, H, E, F):
+    """A layer of few experts in fp32 with 64 tokens (the decode kernels) and with 96: half as many
+    rows again, which took 2.0 to 3.1 times as long where every item was 128 x 128 (now 0.9 to 1.4)."""
+    from paper_2608_21614_amd.device import DeviceLayer
+    from workloads import make_layer
+    calls = []
+    for T in (64, 96):
+        dev = DeviceLayer(make_layer(T, H, E, F, 1, dtype="f32", n_resident=E, residency="random", seed=3))
+        args = dev.args(dev.alloc_outputs())
+        calls.append(lambda dev=dev, args=args: moe.moe_layer_forward(args, dev.ws))
+    few, more = times_us(*calls)
+    print(f"[cliff] fp32 H={H} E={E} F={F}: 64 tokens {few:.1f} us, 96 tokens {more:.1f} us", flush=True)
+    assert more <= 1.7 * few

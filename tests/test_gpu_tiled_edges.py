@@ -47,6 +47,28 @@ def test_tile_edges(moe, dtype, T, H, E, F, k, S, Fs, res):
     run_and_check_layer(moe, lay)
 
 
+# T, H, E, F, k, S, Fs, resident; item shapes of phase 1 and of phase 2 (0: 128 x 128, 1: 128 x 32, 2: 64 x 32)
+F32_SHAPES = [
+    (70, 1024, 16, 1024, 8, 0, 0, 16, 0, 1),     # about 35 rows a group: two and four token blocks
+    (160, 2048, 16, 1024, 8, 0, 0, 16, 0, 0),    # 80 rows: six blocks
+    (230, 2048, 16, 1024, 8, 1, 1024, 16, 0, 0),  # 115 rows: eight blocks, and a second token tile
+    (300, 2048, 4, 1024, 2, 0, 0, 4, 1, 1),      # 150 rows: five tiles of 32
+    (150, 1088, 4, 960, 2, 0, 0, 2, 1, 2),       # widths that leave half a weight tile of 128, none of 64
+    (100, 64, 2, 4096, 1, 0, 0, 2, 2, 2),        # one stage of slabs in phase 1, many in phase 2
+]
+
+
+@pytest.mark.parametrize("T,H,E,F,k,S,Fs,res,ph1,ph2", F32_SHAPES)
+def test_f32_item_shapes(moe, T, H, E, F, k, S, Fs, res, ph1, ph2):
+    from paper_2608_21614_amd.device import to_host
+    print(f"[case] tiled f32 T={T} H={H} E={E} F={F} k={k} S={S} Fs={Fs} resident={res}", flush=True)
+    lay = make_layer(T, H, E, F, k, dtype="f32", shared=S, shared_ffn=Fs, n_resident=res, residency="random",
+                     bias="none", seed=T + H)
+    dev, _, _ = run_and_check_layer(moe, lay, sample=np.arange(0, T, 5))
+    # the tables' header, at the start of the workspace where the scores are the caller's
+    assert to_host(dev.ws[:32].view(torch.int32)).tolist()[3:5] == [ph1, ph2]
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("T,E,k,S,slots", [(70, 12, 3, 2, 5), (150, 64, 8, 0, 3)])
 def test_shared_slots_stay_in_their_room(moe, dtype, T, E, k, S, slots):
