@@ -53,8 +53,8 @@ F32_SHAPES = [
     (160, 2048, 16, 1024, 8, 0, 0, 16, 0, 0),    # 80 rows: six blocks
     (230, 2048, 16, 1024, 8, 1, 1024, 16, 0, 0),  # 115 rows: eight blocks, and a second token tile
     (300, 2048, 4, 1024, 2, 0, 0, 4, 1, 1),      # 150 rows: five tiles of 32
-    (150, 1088, 4, 960, 2, 0, 0, 2, 1, 2),       # widths that leave half a weight tile of 128, none of 64
-    (100, 64, 2, 4096, 1, 0, 0, 2, 2, 2),        # one stage of slabs in phase 1, many in phase 2
+    (150, 1088, 4, 960, 2, 0, 0, 2, 2, 2),       # widths that leave half a weight tile of 128, none of 64
+    (100, 64, 2, 4096, 1, 0, 0, 2, 1, 2),        # one stage of slabs in phase 1, many in phase 2
 ]
 
 
