@@ -1286,6 +1286,7 @@ constexpr int kFLds = 72 * 1024;  // the ring of a workgroup: two workgroups per
 constexpr int kFShapes = 3;
 __host__ __device__ constexpr int shape_rows(int shape) { return shape == 0 ? kFN : 32; }
 __host__ __device__ constexpr int shape_weights(int shape) { return shape < 2 ? kTR : kTR / 2; }
+static_assert(kFN == 128 && kTR == 128, "k_ffn_tiled_f32 shifts by these");
 constexpr int kFFlush = 8;  // slabs between two additions into the second accumulators
 
 __device__ __forceinline__ void mfma_tied_f32(f32x4& acc, float a, float b) {
@@ -1391,6 +1392,7 @@ __global__ void __launch_bounds__(256, 2)
     const uint32_t woff = 16 * (2 * (lane & 31) + (lane >> 5));  // a lane's bytes of a 1 KB weight chunk
     const int n_items = a.tmeta[kDown ? 1 : 0], ng = a.tmeta[2];
     const int shape = a.tmeta[kDown ? 4 : 3], tn = shape_rows(shape), wr = shape_weights(shape);
+    const int ltn = shape == 0 ? 7 : 5, lwt = (shape < 2 ? 7 : 6) - (kDown ? 0 : 1);  // log2 of a token and a weight tile
     const int q0 = gridDim.x / 8;
     int xcd = blockIdx.x % 8;
     const bool few = n_items <= a.cus;
@@ -1413,11 +1415,10 @@ __global__ void __launch_bounds__(256, 2)
         const TileGroup tg = groups[go];
         const bool shared = tg.wsel < 0;
         const int Fg = shared ? a.Fs : a.F;
-        const int ntt = (tg.count + tn - 1) / tn;
         int wt, tt;
-        item_tiles(item - pre[go], weight_tiles(a.H, Fg, kDown, wr), ntt, &wt, &tt);
-        const int n0 = __builtin_amdgcn_readfirstlane(tt) * tn;
-        const int r0 = __builtin_amdgcn_readfirstlane(wt) * (kDown ? wr : wr / 2);
+        item_tiles(item - pre[go], ((kDown ? a.H : Fg) + (1 << lwt) - 1) >> lwt, (tg.count + tn - 1) >> ltn, &wt, &tt);
+        const int n0 = __builtin_amdgcn_readfirstlane(tt) << ltn;
+        const int r0 = __builtin_amdgcn_readfirstlane(wt) << lwt;
         const int K = kDown ? Fg : a.H;
         const int nk = K / 32;
         const size_t wsize = (size_t)(kDown ? 1 : 2) * Fg * a.H;
@@ -1477,9 +1478,6 @@ __global__ void __launch_bounds__(256, 2)
                         tok[i] = q < 0 || t >= a.T ? -1 : t;
                     }
                 }
-                if ((lane & 7) == 0)
-#pragma unroll
-                    for (int i = 0; i < LX; ++i) s_live[8 * (wave * LX + i) + (lane >> 3)] = tok[i] >= 0;
             }
 #pragma unroll
             for (int i = 0; i < LX; ++i)
@@ -1505,6 +1503,9 @@ __global__ void __launch_bounds__(256, 2)
 #pragma unroll
             for (int st = 0; st < S - 1; ++st)
                 if (st < ns) issue(st, st);
+            if (!kDown && (lane & 7) == 0)
+#pragma unroll
+                for (int i = 0; i < LX; ++i) s_live[8 * (wave * LX + i) + (lane >> 3)] = tok[i] >= 0;
             // this lane's first piece of a weight block, and of a token block's row lane % 16
             const uint8_t* aw = sbuf + (lane >> 5) * 1024 + (lane & 31) * 16;
             const uint8_t* bx = sbuf + kTok + (lane & 15) * 128;
