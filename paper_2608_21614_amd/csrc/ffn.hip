@@ -1770,7 +1770,10 @@ hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st)
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
     Args a = make_args(s, fa);
     const int P = s.T * s.k;
-    const int n_pack = (fa.off_rows || fa.off_w) ? (P < 256 ? P : 256) : 0;
+    // pack workgroups: beside the one chain of the fp32 tables, enough to fill the chip with row
+    // copies (24000 rows of 8 KB: 105 us with 256, 61 with 1024)
+    const int pack_max = s.bf16 ? 256 : 1024;
+    const int n_pack = (fa.off_rows || fa.off_w) ? (P < pack_max ? P : pack_max) : 0;
     if (!s.bf16) {
         if (hipError_t e = device_cus(&a.cus); e != hipSuccess) return e;
         hipLaunchKernelGGL(k_tile_groups, dim3((unsigned)(2 + n_pack)), dim3(256), 0, st, a);

@@ -58,3 +58,21 @@ def test_fp32_past_the_decode_batch(moe, H, E, F):
     few, more = times_us(*calls)
     print(f"[cliff] fp32 H={H} E={E} F={F}: 64 tokens {few:.1f} us, 96 tokens {more:.1f} us", flush=True)
     assert more <= 1.7 * few
+
+
+def test_fp32_offloaded_rows_pack_at_the_copy_rate(moe):
+    """What the offloaded rows add to an fp32 prefill layer (about 195 MB written from a batch that
+    the caches hold) against a plain copy of as many bytes: 0.77 of it, and 1.36 with a quarter of
+    the workgroups."""
+    from paper_2608_21614_amd.device import DeviceLayer
+    from workloads import make_layer
+    dev = DeviceLayer(make_layer(4096, 2048, 64, 64, 6, dtype="f32", n_resident=2, residency="random", seed=3))
+    o = dev.alloc_outputs()
+    calls = [lambda a=dev.args(o, pack_offloaded=p): moe.moe_layer_forward(a, dev.ws) for p in (True, False)]
+    calls[0]()
+    torch.cuda.synchronize()
+    n_off = 4096 * 6 - int(o["n_res"][0])
+    src = torch.randn((n_off, 2048), device="cuda")
+    with_pack, without, copy = times_us(*calls, lambda: o["off_rows"][:n_off].copy_(src))
+    print(f"[cliff] fp32 pack of {n_off} rows: {with_pack - without:.1f} us, copy {copy:.1f} us", flush=True)
+    assert with_pack - without <= copy
