@@ -47,9 +47,12 @@ __device__ void pack_row(int q, int P, int k, int row_bytes, const uint8_t* __re
 }
 
 // A decode batch repacked and its offloaded rows packed: workgroup 0 writes the repack's
-// outputs, the others pack rows n_res + g - 1, n_res + g - 1 + (G - 1), ...  Both are chains of
-// a few memory round trips, so one launch instead of two takes little more than the repack
-// alone (256 pairs of 64 tokens, H 2048: 5.2 + 3.8 us and a gap in two launches).
+// outputs, workgroup 1 + i packs row n_res + i (several rows a workgroup had made many wide rows
+// a chain of copies).  Both are chains of a few memory round trips, so one launch instead of two
+// takes no more than the repack alone.  In us, two launches, one with 128 pack workgroups, and now:
+//   64 tokens, 256 pairs, H 2048, bf16:    6.4,  5.0,  4.7
+//   64 tokens, 512 pairs, H 8192, bf16:    8.8,  9.2,  7.2
+//   64 tokens, 512 pairs, H 16384, fp32:  14.9, 25.1, 13.1
 __global__ void __launch_bounds__(256)
     k_repack_pack(int T, int E, int k, int slots, int chunks, const int32_t* __restrict__ topk_idx,
                   const int32_t* __restrict__ expert_slot, int32_t* __restrict__ counts,
@@ -65,9 +68,8 @@ __global__ void __launch_bounds__(256)
     }
     const int nres = repack_chunks<256, true>(T, E, k, slots, 0, chunks, topk_idx, expert_slot, nullptr, nullptr,
                                               nullptr, nullptr, nullptr, s_lds, s_perm);
-    const int P = T * k;
-    for (int p = nres + (int)blockIdx.x - 1; p < P; p += gridDim.x - 1)
-        pack_row(s_perm[p], P, k, row_bytes, x, topk_w, off_rows, off_w, p - nres);
+    const int P = T * k, row = (int)blockIdx.x - 1;
+    if (nres + row < P) pack_row(s_perm[nres + row], P, k, row_bytes, x, topk_w, off_rows, off_w, row);
 }
 
 __global__ void __launch_bounds__(256)
@@ -94,7 +96,7 @@ hipError_t launch_repack(const Shape& s, const int32_t* topk_idx, const int32_t*
     if (P <= 512) {  // a decode batch: up to two chunks of 256
         const int chunks = (P + 255) / 256;
         if (pack)
-            hipLaunchKernelGGL(k_repack_pack, dim3(1 + (P < 128 ? P : 128)), dim3(256), 0, st, s.T, s.E, s.k, s.slots,
+            hipLaunchKernelGGL(k_repack_pack, dim3(1 + P), dim3(256), 0, st, s.T, s.E, s.k, s.slots,
                                chunks, topk_idx, expert_slot, counts, seg_start, perm, inv_perm, n_res, row_bytes, xb,
                                topk_w, ob, off_w);
         else

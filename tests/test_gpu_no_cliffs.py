@@ -76,3 +76,29 @@ def test_fp32_offloaded_rows_pack_at_the_copy_rate(moe):
     with_pack, without, copy = times_us(*calls, lambda: o["off_rows"][:n_off].copy_(src))
     print(f"[cliff] fp32 pack of {n_off} rows: {with_pack - without:.1f} us, copy {copy:.1f} us", flush=True)
     assert with_pack - without <= copy
+
+
+def test_repack_of_wide_rows_either_side_of_one_launch(moe):
+    """moe_repack with offloaded rows of 64 KB: 512 pairs (one launch) against 520 (two): 0.9 times as
+    long, and 1.7 where 128 workgroups packed the rows."""
+    graphs = []
+    for T in (64, 65):
+        E, k, H, r = 128, 8, 16384, 16
+        P = T * k
+        dims = moe.make_dims(T, H, E, 64, k, slots=r, dtype=moe.MOE_F32)
+        g = torch.Generator().manual_seed(T)
+        idx = torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).int().cuda()
+        slot = torch.full((E,), -1, dtype=torch.int32)
+        slot[:r] = torch.arange(r, dtype=torch.int32)
+        i32 = [torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E, P, P, 1)]
+        x, rows = torch.randn((T, H), device="cuda"), torch.empty((P, H), device="cuda")
+        w, off_w, slot = torch.rand((T, k), device="cuda"), torch.empty(P, device="cuda"), slot.cuda()
+        keep = (idx, slot, i32, x, rows, w, off_w)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                moe.moe_repack(dims, idx, w, slot, x, *i32, rows, off_w)
+        graphs.append((graph, keep))
+    one, two = times_us(*(lambda g=g: g.replay() for g, _ in graphs))
+    print(f"[cliff] repack of 64 KB rows: 512 pairs {one / 10:.1f} us, 520 pairs {two / 10:.1f} us", flush=True)
+    assert one <= 1.3 * two
