@@ -1757,15 +1757,6 @@ size_t ffn_tile_meta_bytes(const Shape& s) {
 
 size_t ffn_tile_claim_bytes(const Shape& s) { return use_tiled(s) ? 2 * 8 * kTClaimPitch * sizeof(int32_t) : 0; }
 
-// CUs of the current device, the same number on each of its eight XCDs.
-static hipError_t device_cus(int* cus) {
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e == hipSuccess) *cus = std::max(*cus / 8 * 8, 8);
-    return e;
-}
-
 hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
     Args a = make_args(s, fa);

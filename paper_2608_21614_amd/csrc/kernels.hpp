@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace saem {
 
 // Shapes of one layer, already validated by the ABI.
@@ -12,6 +14,15 @@ struct Shape {
     int T, H, E, F, k, S, Fs, slots;
     int bf16;  // 1: bf16 activations and weights, 0: fp32
 };
+
+// CUs of the current device, the same number on each of its eight XCDs.
+inline hipError_t device_cus(int* cus) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipDeviceGetAttribute(cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e == hipSuccess) *cus = std::max(*cus / 8 * 8, 8);
+    return e;
+}
 
 // Decode batches (T <= 64) route through K-sliced partial scores: the number of
 // slices (0 for larger batches); their scratch is [slices][64][E] fp32.

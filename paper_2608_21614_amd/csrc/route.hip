@@ -4,9 +4,10 @@
 // Scores run on MFMA (v_mfma_f32_16x16x32_bf16, or v_mfma_f32_16x16x4_f32 for
 // fp32 inputs): router rows are the M side, 16 tokens the N side.
 //
-//  * T > 64 (prefill): k_router_scores, one workgroup per 16 tokens x 16, 32 or 64 experts
-//    whose 16 waves split K and add their partial tiles in a fixed order, writes the
-//    scores; then k_route_finish picks the top-k, one wave per token over many CUs.
+//  * T > 64 (prefill): k_router_scores, one workgroup per 8, 16 or 32 tokens x 16, 32 or 64
+//    experts whose 16 waves split K and add their partial tiles in a fixed order, writes the
+//    scores.  With all of a token's scores in one workgroup (up to 64 experts) it also picks the
+//    top-k; else, and from the caller's scores, k_route_finish does, one wave per token.
 //  * T <= 64 (decode): k_router_partial spreads the scores over one workgroup
 //    per K slice (a single CU cannot stream the batch and the router fast
 //    enough), then k_route_finish adds each token's slices in order and runs its
@@ -281,43 +282,54 @@ void launch_finish(const Shape& s, const float* part, int nsl, const float* bias
 }
 
 // Prefill routing.  A CU draws about 64 KB per microsecond of such loads, so what counts is
-// the bytes of the fullest CU: (tokens + experts of a workgroup) x H.
-//  * Up to 64 experts a workgroup has all scores of its tokens and picks their top-k itself,
-//    for 8 tokens (half an MFMA tile) while that leaves at most 512 workgroups, then 16 or
-//    32.  At 8192 x 64 x H 2048, 32 tokens take 22 us; two launches take 16 + 8 + the gap.
-//  * With 17 to 64 experts whose rows are long (8 KB or more) and fewer than 4096 tokens, the
-//    smaller loads of 16 tokens x 32 experts pay for the second launch: 2048 x 64 x H 2048
-//    in fp32 14.0 + 4.6 us against 25.4 (in bf16 8.4 + 4.7 + the gap against 14).
+// the bytes of the fullest CU: (tokens + experts of a workgroup) x H, times its workgroups.
+//  * Up to 64 experts a workgroup can have all scores of its tokens and pick their top-k itself,
+//    for 8 tokens (half an MFMA tile) while every CU gets at most one workgroup, then 16, then 32.
+//    In us at H 2048, 8 / 16 / 32 tokens a workgroup:
+//      64 experts, bf16: 2047 tokens 13.0 / 14.7 / 19.7;   2049: 22.1 / 14.6 / 19.6;   4095:
+//      24.2 / 15.3 / 20.2;   4097: 32.8 / 24.4 / 20.4;   8191: 46.5 / 28.4 / 21.0;   12000: 68 / 41 / 38
+//    Up to 16 experts take little enough LDS for several workgroups on a CU, so 16 tokens stay ahead:
+//      8 experts, bf16: 2047 tokens 6.2 / 7.5 / 10.7;   8193: 14.8 / 11.3 / 13.1;   16384: 24 / 18 / 22
+//  * The smaller loads of tiles over fewer experts pay for a second launch (the top-k) where a
+//    workgroup's rows are many bytes.  All experts at once / tiles and top-k, in us:
+//      at most one 8-token workgroup per CU: bf16 168 KB 9.5 / 9.0, 200 KB (17 experts, H 4096)
+//        10.6 / 12.5, 216 KB (64, H 1536) 10.6 / 8.3; fp32 100 KB (17, H 1024) 9.4 / 10.2, 150 KB
+//        (17, H 1536) 12.0 / 11.1, 246 KB (33, H 1536) 18.2 / 11.5, 576 KB (64, H 2048) 23 / 13
+//      one 16-token workgroup: bf16 320 KB 15 / 17, fp32 400 KB 24 / 21 to 26, 640 KB 28 / 28,
+//        784 KB (33, H 4096) 42 / 35
 //  * More than 64 experts: the largest tile that still gives every CU a workgroup, then the
 //    top-k in a launch of its own.
 template <typename Elt>
-void launch_prefill(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
-                    int32_t* topk_idx, float* topk_w, hipStream_t st) {
+hipError_t launch_prefill(const Shape& s, const void* x, const void* w_router, const float* bias, float* logits,
+                          int32_t* topk_idx, float* topk_w, hipStream_t st) {
+    int cus = 0;
+    if (hipError_t e = device_cus(&cus); e != hipSuccess) return e;
     auto tiles = [&](int n, int tile) { return (n + tile - 1) / tile; };
     auto go = [&](auto kernel, int rows, int m) {
         hipLaunchKernelGGL(kernel, dim3(tiles(s.T, rows), tiles(s.E, 16 * m)), dim3(kScoreWaves * kWave), 0, st, s.T,
                            s.H, s.E, rows, static_cast<const Elt*>(x), static_cast<const Elt*>(w_router), bias, logits,
                            s.k, topk_idx, topk_w);
     };
-    const bool long_rows = (size_t)s.H * sizeof(Elt) >= 8192;
-    if (s.E <= 16 || (s.E <= 64 && (s.T >= 4096 || !long_rows))) {
-        const int rows = s.T >= 8192 ? 32 : (s.T >= 4096 ? 16 : 8);
+    const int rows = s.T <= 8 * cus ? 8 : (s.T <= 16 * cus || s.E <= 16 ? 16 : 32);
+    const size_t bytes = (size_t)(s.E + rows) * s.H * sizeof(Elt);  // a workgroup's, with all experts
+    const size_t limit = rows == 8 ? (sizeof(Elt) == 2 ? 200 : 144) << 10 : (rows == 16 ? 640 << 10 : SIZE_MAX);
+    if (s.E <= 16 || (s.E <= 64 && bytes <= limit)) {
         if (rows == 32) {
-            if (s.E <= 16) go(k_router_scores<Elt, 1, 2, true>, rows, 1);
-            else if (s.E <= 32) go(k_router_scores<Elt, 2, 2, true>, rows, 2);
+            if (s.E <= 32) go(k_router_scores<Elt, 2, 2, true>, rows, 2);
             else go(k_router_scores<Elt, 4, 2, true>, rows, 4);
         } else {
             if (s.E <= 16) go(k_router_scores<Elt, 1, 1, true>, rows, 1);
             else if (s.E <= 32) go(k_router_scores<Elt, 2, 1, true>, rows, 2);
             else go(k_router_scores<Elt, 4, 1, true>, rows, 4);
         }
-        return;
+        return hipGetLastError();
     }
-    if (tiles(s.T, 32) * tiles(s.E, 64) >= 256) go(k_router_scores<Elt, 4, 2, false>, 32, 4);
-    else if (tiles(s.T, 16) * tiles(s.E, 64) >= 256) go(k_router_scores<Elt, 4, 1, false>, 16, 4);
-    else if (tiles(s.T, 16) * tiles(s.E, 32) >= 256) go(k_router_scores<Elt, 2, 1, false>, 16, 2);
+    if (tiles(s.T, 32) * tiles(s.E, 64) >= cus) go(k_router_scores<Elt, 4, 2, false>, 32, 4);
+    else if (tiles(s.T, 16) * tiles(s.E, 64) >= cus) go(k_router_scores<Elt, 4, 1, false>, 16, 4);
+    else if (tiles(s.T, 16) * tiles(s.E, 32) >= cus) go(k_router_scores<Elt, 2, 1, false>, 16, 2);
     else go(k_router_scores<Elt, 1, 1, false>, 16, 1);
     launch_finish(s, nullptr, 0, nullptr, logits, true, topk_idx, topk_w, st);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -334,9 +346,10 @@ hipError_t launch_route_topk(const Shape& s, const void* x, const void* w_router
                              bool logits_in, int32_t* topk_idx, float* topk_w, float* part, hipStream_t st) {
     if (s.T == 0) return hipSuccess;
     if (!front_small_fits(s)) {
-        if (logits_in) launch_finish(s, nullptr, 0, nullptr, logits, true, topk_idx, topk_w, st);
-        else if (s.bf16) launch_prefill<uint16_t>(s, x, w_router, bias, logits, topk_idx, topk_w, st);
-        else launch_prefill<float>(s, x, w_router, bias, logits, topk_idx, topk_w, st);
+        if (!logits_in)
+            return s.bf16 ? launch_prefill<uint16_t>(s, x, w_router, bias, logits, topk_idx, topk_w, st)
+                          : launch_prefill<float>(s, x, w_router, bias, logits, topk_idx, topk_w, st);
+        launch_finish(s, nullptr, 0, nullptr, logits, true, topk_idx, topk_w, st);
         return hipGetLastError();
     }
     const int nsl = router_slices(s);
