@@ -1302,16 +1302,19 @@ __device__ __forceinline__ void lds_load_1k_lanes(uint32_t lds, const void* p) {
 }
 
 // The item shape of a phase: the first whose longest item is at most so many times a CU's share of
-// the phase's work, else the last.  Times at a longest item of so many shares, 128 x 128, 128 x 32
-// and 64 x 32 in us:
-//   1.1: 152, 163, 180 (16 experts, H 2048, F 128, phase 1);   1.3: 67, 70, 80 (4 experts x 75
-//   rows, H 1024, phase 1) and 245, 263, 279 (8 x 83, H 4096, phase 2);   1.6: 40, 47, 47 (64 x 64,
-//   H 512);   1.9: 79, 69, 69 (4 x 179, H 1024);   2.2: 116, 68, 74;   above that 128 x 128 loses more;
+// the phase's work, else the last.  Full 128 x 128 tiles take half the LDS reads of 128 x 32 ones
+// and win where a CU has several in turn; with one or two per CU, unequal ones leave CUs idle, which
+// counts for less where an item's fixed costs (some 8 us) weigh more, at small K.  Times at a longest
+// item of so many shares, 128 x 128 and 128 x 32 in us:
+//   K above 512: 0.4: 445, 490 (8 x 83 rows, H 4096, F 4096);   0.6: 599, 512 (64 x 86, H 4096, F 512);
+//     1.0 to 1.3: 509, 370 (8 x 128, H 4096, F 2048); 751, 345 (2 x 143, H 6144, F 4096); 137, 105 (64 x
+//     8 + 2 shared x 1014, H 1536); 245, 263 (8 x 83, phase 2);   1.4: 569, 592 (4 x 173, H 8192)
+//   K to 512: 1.1: 109, 85;   1.4: 21, 25;   1.6: 40, 47 (64 x 64, H 512);   1.9: 79, 69;   2.2: 116, 68
 // and of the second shape's longest item, 128 x 32 and 64 x 32:
 //   0.8: 20, 21;   1.0: 25, 31 and 78, 73;   1.1: 21, 22;   1.3: 52, 51 and 38, 35;   1.6: 36, 24.
 // By every thread of the workgroup; s_red: 4 kFShapes floats.
 __device__ int item_shape(const Args& a, int ng, const int* s_rows, bool down, float* s_red) {
-    constexpr float kShare[kFShapes - 1] = {1.6f, 1.2f};
+    const float limit[kFShapes - 1] = {(down ? a.Fa : a.H) <= 512 ? 1.6f : 0.8f, 1.5f};
     constexpr int N = kFShapes;
     float v[N] = {};  // work, and each shape's longest item per weight row
     for (int gi = threadIdx.x; gi < ng; gi += 256) {
@@ -1338,7 +1341,7 @@ __device__ int item_shape(const Args& a, int ng, const int* s_rows, bool down, f
     for (; shape < kFShapes - 1; ++shape) {
         const int i = 1 + shape;
         const float longest = fmaxf(fmaxf(s_red[i], s_red[N + i]), fmaxf(s_red[2 * N + i], s_red[3 * N + i]));
-        if (longest * shape_weights(shape) <= kShare[shape] * share) break;
+        if (longest * shape_weights(shape) <= limit[shape] * share) break;
     }
     return shape;
 }

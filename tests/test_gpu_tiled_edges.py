@@ -49,9 +49,11 @@ def test_tile_edges(moe, dtype, T, H, E, F, k, S, Fs, res):
 
 # T, H, E, F, k, S, Fs, resident; item shapes of phase 1 and of phase 2 (0: 128 x 128, 1: 128 x 32, 2: 64 x 32)
 F32_SHAPES = [
-    (70, 1024, 16, 1024, 8, 0, 0, 16, 0, 1),     # about 35 rows a group: two and four token blocks
-    (160, 2048, 16, 1024, 8, 0, 0, 16, 0, 0),    # 80 rows: six blocks
-    (230, 2048, 16, 1024, 8, 1, 1024, 16, 0, 0),  # 115 rows: eight blocks, and a second token tile
+    (280, 512, 64, 512, 8, 0, 0, 64, 0, 0),      # about 35 rows a group: two and four token blocks
+    (600, 512, 64, 512, 8, 0, 0, 64, 0, 0),      # 75 rows: four and six blocks
+    (920, 448, 64, 512, 8, 1, 448, 64, 0, 0),    # 115 rows: six, eight, and a second token tile
+    (500, 1024, 64, 1024, 8, 0, 0, 64, 0, 0),    # longer sums
+    (160, 2048, 16, 1024, 8, 0, 0, 16, 1, 1),
     (300, 2048, 4, 1024, 2, 0, 0, 4, 1, 1),      # 150 rows: five tiles of 32
     (150, 1088, 4, 960, 2, 0, 0, 2, 2, 2),       # widths that leave half a weight tile of 128, none of 64
     (100, 64, 2, 4096, 1, 0, 0, 2, 1, 2),        # one stage of slabs in phase 1, many in phase 2
