@@ -2,13 +2,15 @@
 
 The ABI allows calls on distinct streams with distinct workspaces to run at the
 same time: the library keeps no device or host state between calls, and a call
-writes only its outputs and its workspace.  Three threads start together and
+writes only its outputs and its workspace.  Five threads start together and
 each enqueues eight layer calls on its own stream without synchronising in
 between:
   * a bf16 decode layer with a shared expert and offloaded experts,
   * the same layer's weights (read by both at once) on another input batch,
     with a second workspace,
-  * a bf16 prefill layer.
+  * a bf16 prefill layer,
+  * an fp32 prefill layer (its tables lie in the workspace's room for the scores),
+  * the same fp32 layer on another input batch, with a second workspace.
 Every output must equal the same call made alone, bit for bit (the path is
 deterministic).
 """
@@ -42,13 +44,15 @@ def test_threads_on_own_streams_and_workspaces_match_serial_calls():
     dec = make_layer(40, 256, 16, 512, 4, "bf16", shared=1, shared_ffn=256, n_resident=10, residency="random",
                      bias="zipf", seed=5)
     pre = make_layer(130, 256, 8, 256, 2, "bf16", n_resident=6, residency="random", seed=6)
-    d_dec, d_pre = DeviceLayer(dec), DeviceLayer(pre)
-    ws2 = torch.empty_like(d_dec.ws)
-    x2 = to_device(np.ascontiguousarray(dec.x[::-1]))
+    pre32 = make_layer(300, 512, 64, 256, 8, "f32", shared=1, shared_ffn=128, n_resident=40, residency="random", seed=7)
+    d_dec, d_pre, d_pre32 = DeviceLayer(dec), DeviceLayer(pre), DeviceLayer(pre32)
+    ws2, ws32 = torch.empty_like(d_dec.ws), torch.empty_like(d_pre32.ws)
+    x2, x32 = (to_device(np.ascontiguousarray(lay.x[::-1])) for lay in (dec, pre32))
 
     # (layer, workspace, input or None) per thread
-    jobs = [(d_dec, d_dec.ws, None), (d_dec, ws2, x2), (d_pre, d_pre.ws, None)]
-    say("decode T 40, same weights on a second input, prefill T 130")
+    jobs = [(d_dec, d_dec.ws, None), (d_dec, ws2, x2), (d_pre, d_pre.ws, None),
+            (d_pre32, d_pre32.ws, None), (d_pre32, ws32, x32)]
+    say("decode T 40, same weights on a second input, prefill T 130, fp32 prefill T 300 twice")
 
     refs = []
     for dev, ws, x in jobs:                     # each call alone

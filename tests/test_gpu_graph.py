@@ -27,6 +27,11 @@ CASES = {
     "decode_bf16_shared_offloaded": lambda: make_layer(40, 256, 16, 512, 4, "bf16", shared=1, shared_ffn=256,
                                                        n_resident=10, residency="random", bias="zipf", seed=3),
     "prefill_bf16": lambda: make_layer(130, 256, 8, 256, 2, "bf16", n_resident=6, residency="random", seed=4),
+    "prefill_f32": lambda: make_layer(130, 256, 8, 256, 2, "f32", shared=1, shared_ffn=128, n_resident=6,
+                                      residency="random", seed=4),
+    # more items than workgroups: the replays claim from counters that the replay before left used
+    "prefill_f32_claims": lambda: make_layer(520, 512, 64, 512, 8, "f32", n_resident=60, residency="random", seed=4),
+    "prefill_bf16_claims": lambda: make_layer(200, 512, 64, 1024, 8, "bf16", n_resident=60, residency="random", seed=4),
 }
 
 

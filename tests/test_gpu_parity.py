@@ -227,6 +227,40 @@ def test_offload_pack_bit_exact(moe):
     check_offloaded_list(lay.x, k, _host(perm), n_res, _host(off_rows), _host(off_w), _host(d_w))
 
 
+@pytest.mark.parametrize("T,k,off", [(40, 2, "both"), (64, 8, "both"), (64, 8, "rows"), (3, 4, "gates"), (90, 8, "both")])
+def test_repack_drops_ids_and_packs_the_rest(moe, T, k, off):
+    """moe_repack with ids outside [0, E) and the offloaded rows asked for: the rows and gates of the
+    offloaded pairs that there are, in packed order, and the room past them untouched (up to 512
+    pairs in one launch, above in two)."""
+    say("repack with dropped ids", T, k, off)
+    E, H = 12, 64
+    rng = np.random.default_rng(T + k)
+    idx = np.stack([rng.choice(E, k, replace=False) for _ in range(T)]).astype(np.int32)
+    idx.reshape(-1)[rng.choice(T * k, 5, replace=False)] = [-1, E, E + 7, -9, 2**30]
+    slot = np.full(E, -1, np.int32)
+    slot[[1, 4, 7]] = [2, 0, 1]
+    x, w = rng.standard_normal((T, H)).astype(np.float32), rng.random((T, k)).astype(np.float32)
+    P = T * k
+    dims = moe.make_dims(T, H, E, 64, k, slots=3, dtype=0)
+    i32 = [torch.empty(n, dtype=torch.int32, device="cuda") for n in (E, E, P, P, 1)]
+    rows = torch.full((P, H), -5.0, device="cuda") if off != "gates" else None
+    gates = torch.full((P,), -5.0, device="cuda") if off != "rows" else None
+    moe.moe_repack(dims, _dev(idx), _dev(w), _dev(slot), _dev(x), *i32, rows, gates)
+    torch.cuda.synchronize()
+    flat, res = idx.reshape(-1), slot >= 0
+    order = [q for part in (res, ~res) for e in np.flatnonzero(part) for q in np.flatnonzero(flat == e)]
+    n_res = int(sum((flat == e).sum() for e in np.flatnonzero(res)))
+    np.testing.assert_array_equal(_host(i32[2]), order + [-1] * (P - len(order)))
+    assert int(_host(i32[4])[0]) == n_res
+    off_q = np.array(order[n_res:])
+    if rows is not None:
+        np.testing.assert_array_equal(_host(rows)[:len(off_q)], x[off_q // k])
+        assert (_host(rows)[len(off_q):] == -5.0).all()
+    if gates is not None:
+        np.testing.assert_array_equal(_host(gates)[:len(off_q)], w.reshape(-1)[off_q])
+        assert (_host(gates)[len(off_q):] == -5.0).all()
+
+
 # ---------------------------------------------------------------------------
 # fused layer forward
 # ---------------------------------------------------------------------------
@@ -486,6 +520,51 @@ def test_layer_logits_in_routes_given_scores(moe):
     np.testing.assert_array_equal(_host(o["topk_idx"]), ref["idx"])
     np.testing.assert_array_equal(_host(o["perm"]), ref["perm"])
     assert rel_l2(host_f64(o["out"]), ref["out_res"]) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("dtype,T,E,k", [("bf16", 100, 40, 6), ("f32", 100, 40, 6), ("f32", 65, 100, 4)])
+def test_layer_logits_in_prefill(moe, dtype, T, E, k):
+    """MOE_LOGITS_IN past the decode batch: the fused forward routes caller scores with exact ties
+    bit-exactly and leaves them as they are."""
+    from paper_2608_21614_amd.device import DeviceLayer
+    say("layer logits-in, prefill", dtype, T, E, k)
+    lay = make_layer(T, 128, E, 192, k, dtype=dtype, shared=1, shared_ffn=64, n_resident=E // 2, residency="random",
+                     seed=9)
+    dev = DeviceLayer(lay)
+    o = dev.alloc_outputs()
+    lg = np.round(np.random.default_rng(T).standard_normal((T, E)) * 2).astype(np.float32)  # integers: many ties
+    o["logits"].copy_(_dev(lg))
+    dev.forward(o, logits_in=True)
+    torch.cuda.synchronize()
+    ref = oracle.layer_forward_synthetic(lay, logits=lg.astype(np.float64), offloaded=False)
+    np.testing.assert_array_equal(_host(o["topk_idx"]), ref["idx"])
+    np.testing.assert_array_equal(_host(o["perm"]), ref["perm"])
+    np.testing.assert_array_equal(_host(o["logits"]), lg)
+    assert rel_l2(host_f64(o["out"]), ref["out_res"]) <= TOL[dtype]
+
+
+@pytest.mark.parametrize("T,H,E,F,k,S", [(65, 128, 1, 64, 1, 8), (65, 128, 4, 64, 2, 0), (300, 256, 16, 192, 4, 2),
+                                         (520, 512, 64, 256, 8, 0)])
+def test_f32_prefill_scores_in_the_workspace(moe, T, H, E, F, k, S):
+    """fp32 prefill without output arrays for the scores and the routing: the FFN's tables then take
+    the room of the scores, on a workspace of garbage, twice, with the same outputs as with the
+    caller's arrays.  The first shape has the least room (260 bytes of scores, 248 of tables)."""
+    from paper_2608_21614_amd.device import DeviceLayer
+    say("fp32 prefill, scores in the workspace", T, H, E, F, k, S)
+    lay = make_layer(T, H, E, F, k, dtype="f32", shared=S, shared_ffn=64 if S else 0, n_resident=E, residency="random",
+                     seed=T)
+    dev = DeviceLayer(lay)
+    o, plain = dev.alloc_outputs(), dev.alloc_outputs()
+    dev.forward(o)
+    args = moe.layer_args(dev.dims, dev.x, dev.w_router, dev.bias, dev.expert_slot, dev.w13, dev.w2, dev.ws13, dev.ws2,
+                          plain["out"], plain["out_dtype"])
+    for fill in (0xA5, 0xFF):
+        dev.ws.fill_(fill)
+        plain["out"].fill_(7.0)
+        for _ in range(2):
+            moe.moe_layer_forward(args, dev.ws)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(_host(plain["out"]), _host(o["out"]))
 
 
 # ---------------------------------------------------------------------------
