@@ -593,9 +593,9 @@ def measure_workload(name, cfg, args, steps: int, warmup: int, cpu_seconds: floa
     p1_s = p1_us * 1e-6
     traffic = read_traffic(name)
     if cfg.tokens > 64:
-        # prefill-size batches run MFMA kernels at the ridge (bf16: the tiled kernel; fp32: the
-        # stream kernel over 64-row chunks): FLOP rate against the dense matrix-core peak of the
-        # layer's type, and the HBM fraction beside it
+        # prefill-size batches run MFMA kernels at the ridge (a tiled one for each data type):
+        # FLOP rate against the dense matrix-core peak of the layer's type, and the HBM
+        # fraction beside it
         achieved = alg["phase1_flops"] / p1_s / 1e12
         peak = mfma_peak_tflops(cfg.dtype)
         kname = ("k_ffn_tiled (phase 1: gate/up projections + SwiGLU)" if cfg.dtype == "bf16" else

@@ -69,7 +69,9 @@ Layout layout_of(const Shape& s) {
         off = align256(off + std::max<size_t>(bytes, 1));
         return at;
     };
-    L.logits = take(T * E * 4);
+    // scores; fp32 prefill: the tiled FFN's tables take their room once the routing is done
+    // (4 T E bytes with T > 64 always hold them: 32 + 24 a group)
+    L.logits = take(std::max(T * E * 4, s.bf16 ? size_t(0) : saem::ffn_tile_meta_bytes(s)));
     L.idx = take(T * k * 4);
     L.w = take(T * k * 4);
     L.counts = take(E * 4);
@@ -77,11 +79,11 @@ Layout layout_of(const Shape& s) {
     L.nres = take(4);
     L.perm = take(T * k * 4);
     L.inv = take(T * k * 4);
-    // decode: the router's partial scores; bf16 prefill: the tiled FFN's claim counters
+    // decode: the router's partial scores; prefill: the tiled FFN's claim counters
     L.part = take(std::max((size_t)saem::router_slices(s) * 64 * E * 4, saem::ffn_tile_claim_bytes(s)));
     L.act = take((size_t)saem::ffn_act_rows(s) * L.Fa * (s.bf16 ? 2 : 4));
     L.xg = take((size_t)saem::ffn_gather_rows(s) * H * 2);
-    L.meta = take(saem::ffn_tile_meta_bytes(s));
+    L.meta = take(s.bf16 ? saem::ffn_tile_meta_bytes(s) : 0);
     L.y = take(saem::ffn_y_bytes(s));
     L.total = off;
     return L;
@@ -93,7 +95,7 @@ T* at(void* ws, size_t off) {
 }
 
 // The tiled FFN's tables.  The fp32 ones (a few words a group) take the room of the scores,
-// which nothing reads once the routing is done: 4 T E bytes, T > 64, against 32 + 24 (E + S).
+// which nothing reads once the routing is done.
 int32_t* tile_meta(const Shape& s, const Layout& L, void* ws) { return at<int32_t>(ws, s.bf16 ? L.meta : L.logits); }
 
 moe_status hip_status(hipError_t e) { return e == hipSuccess ? MOE_OK : MOE_ERR_HIP; }

@@ -72,8 +72,8 @@ struct Args {
     int max_routed;   // routed groups the grid reserves (>= active resident experts)
     int ipg_r;        // items (workgroups) per routed group
     int ipg_s;        // items per shared group
-    // offloaded-row pack done by the workgroups past the FFN items (phase 1; phase 2
-    // in the fused path)
+    // offloaded-row pack done by the workgroups past the FFN items (phase 2 of the fused
+    // decode path), or beside the tiled kernels' tables
     const float* topk_w;
     const int32_t* n_res;
     void* off_rows;
@@ -125,10 +125,9 @@ struct Group {
 };
 
 // Active resident routed experts (ascending id) into s_list; returns their number.
-// With s_info, entry i also gets expert s_list[i]'s (segment start, count, slot),
-// read in the same round trip as the counts.
+// s_info[i]: expert s_list[i]'s (segment start, count, slot), read in the same round trip.
 // Must be called by all threads of a 256-thread workgroup.
-__device__ int list_active(const Args& a, int* s_list, int* s_wsum, int4* s_info = nullptr) {
+__device__ int list_active(const Args& a, int* s_list, int* s_wsum, int4* s_info) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id();
     const int e = tid;
     bool act = false;
@@ -136,7 +135,7 @@ __device__ int list_active(const Args& a, int* s_list, int* s_wsum, int4* s_info
     if (e < a.E) {
         sl = a.expert_slot[e];
         cnt = a.counts[e];
-        if (s_info) seg = a.seg_start[e];
+        seg = a.seg_start[e];
         act = is_resident(sl, a.slots) && cnt > 0;
     }
     const unsigned long long b = __ballot(act);
@@ -147,7 +146,7 @@ __device__ int list_active(const Args& a, int* s_list, int* s_wsum, int4* s_info
     if (act) {
         const int pos = base + __popcll(b & ((1ull << lane) - 1ull));
         s_list[pos] = e;
-        if (s_info) s_info[pos] = make_int4(seg, cnt, sl, 0);
+        s_info[pos] = make_int4(seg, cnt, sl, 0);
     }
     const int n = s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3];
     __syncthreads();
@@ -385,7 +384,7 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
                 repack_chunks<256>(a.T, a.E, a.k, a.slots, 0, (a.T * a.k + 255) / 256, a.topk_idx, a.expert_slot,
                                    a.rp_counts, a.rp_seg_start, a.rp_perm, a.rp_inv_perm, a.rp_n_res,
                                    reinterpret_cast<int*>(s_raw));
-        } else if (a.fused == (int)kDown) {  // trailing workgroups pack the offloaded rows
+        } else if (a.fused) {  // trailing workgroups of phase 2 pack the offloaded rows
             pack_offloaded(a, item - n_items, gridDim.x - n_items, sizeof(Elt));
         }
         return;
@@ -685,8 +684,14 @@ __global__ void __launch_bounds__(256, 2) k_ffn_stream(Args a) {
 // (phase 2 storing bf16 rows).  A copy without the MFMAs takes 572 instead of 625 us in the first
 // line and the same 107 in the fourth: the loads bound the kernel throughout.
 // The weights of an item of up to 64 rows are loaded non-temporally (118 -> 108 us for
-// phase 1 at 40 rows a group, 79 -> 72 at 16; phase 2 63 -> 66 and 51 -> 42): they are read
-// once.  With more rows it gained nothing (128 -> 122 and 69 -> 80 us at 100 rows).
+// phase 1 at 40 rows a group, 79 -> 72 at 16; phase 2 63 -> 66 and 51 -> 42): a group of so few
+// rows reads them once.  (So does the short last tile of a longer group, whose other items read
+// the same panel; it is one item in two at most.)  With more rows it gained nothing (128 -> 122
+// and 69 -> 80 us at 100 rows).
+//
+// Registers: the widest copies fill the 256 of two waves per SIMD.  The compiler spills 4 (phase
+// 1) and 7 (phase 2) vector registers to scratch, all outside the K loop, and 41 and 20 scalars to
+// lanes of a vector register, of which the K loop reads back two to six per two slabs.
 //
 // The gathered rows, the activations and the expert outputs are stored non-temporally: the next
 // launch reads them, from other XCDs, and here they would push the panels out of the L2
@@ -1748,7 +1753,8 @@ long long ffn_gather_rows(const Shape& s) {
 }
 
 size_t ffn_tile_meta_bytes(const Shape& s) {
-    if (!tiled_bf16(s)) return 0;
+    if (!use_tiled(s)) return 0;
+    if (!s.bf16) return kTHeader * 4 + (sizeof(TileGroup) + 2 * 4) * (size_t)(max_routed_groups(s) + s.S);
     const size_t need = kTHeader * 4 + sizeof(TileGroup) * (size_t)(max_routed_groups(s) + s.S) +
                         sizeof(TileItem) * (size_t)(tiled_items(s, false) + tiled_items(s, true));
     // the workspace of a shape is part of the interface (the fixed scratch array accepts or
@@ -1763,13 +1769,13 @@ size_t ffn_tile_claim_bytes(const Shape& s) { return use_tiled(s) ? 2 * 8 * kTCl
 hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st) {
     if (s.T == 0 || !use_tiled(s)) return hipSuccess;
     Args a = make_args(s, fa);
+    if (hipError_t e = device_cus(&a.cus); e != hipSuccess) return e;
     const int P = s.T * s.k;
     // pack workgroups: beside the one chain of the fp32 tables, enough to fill the chip with row
     // copies (24000 rows of 8 KB: 105 us with 256, 61 with 1024)
     const int pack_max = s.bf16 ? 256 : 1024;
     const int n_pack = (fa.off_rows || fa.off_w) ? (P < pack_max ? P : pack_max) : 0;
     if (!s.bf16) {
-        if (hipError_t e = device_cus(&a.cus); e != hipSuccess) return e;
         hipLaunchKernelGGL(k_tile_groups, dim3((unsigned)(2 + n_pack)), dim3(256), 0, st, a);
         return hipGetLastError();
     }
@@ -1777,7 +1783,7 @@ hipError_t launch_ffn_prepare(const Shape& s, const FfnArgs& fa, hipStream_t st)
     // about two workgroups per CU over the blocks that the batch needs at least, of eight
     // 32-column blocks or more each
     const long long least = ((long long)P * (a.max_routed > 0) + (s.S > 0 ? s.T : 0) + 15) / 16;
-    long long split = least > 0 ? 512 / least : 1;
+    long long split = least > 0 ? 2 * a.cus / least : 1;
     if (split > s.H / 256) split = s.H / 256;
     if (split < 1) split = 1;
     hipLaunchKernelGGL(k_gather_tokens, dim3((unsigned)(kTabWgs + blocks * split + n_pack)), dim3(256), 0, st, a, kTabWgs,
@@ -1825,9 +1831,9 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
         a.ipg_r = s.F / (8 * mt);
         a.ipg_s = s.S > 0 ? s.Fs / (8 * mt) : 1;
         const int P = s.T * s.k;
-        const int n_pack = (fa.off_rows || fa.off_w) ? (P < 64 ? P : 64) : 0;  // pack workgroups (P >= 1)
-        // phase 1, then (fused) the repack workgroup, or the pack workgroups
-        int grid = a.max_routed * a.ipg_r + s.S * a.ipg_s + (a.fused ? 1 : n_pack);
+        const int n_pack = (a.fused && (fa.off_rows || fa.off_w)) ? (P < 64 ? P : 64) : 0;  // pack workgroups (P >= 1)
+        // phase 1, then (fused) the repack workgroup
+        int grid = a.max_routed * a.ipg_r + s.S * a.ipg_s + (a.fused ? 1 : 0);
         if (grid > 0) {
             if (s.bf16) launch_stream<uint16_t, false>(nt, sw, grid, a, st);
             else launch_stream<float, false>(nt, sw, grid, a, st);
@@ -1837,7 +1843,7 @@ hipError_t launch_grouped_ffn(const Shape& s, const FfnArgs& fa, hipStream_t st,
         // workgroups, which read the perm and n_res that phase 1 wrote
         a.ipg_r = (s.H / (16 * mt)) * a.ks;
         a.ipg_s = (s.H / (16 * mt)) * a.ks;
-        grid = a.max_routed * a.ipg_r + s.S * a.ipg_s + (a.fused ? n_pack : 0);
+        grid = a.max_routed * a.ipg_r + s.S * a.ipg_s + n_pack;
         if (grid > 0) {
             if (s.bf16) launch_stream<uint16_t, true>(nt, sw, grid, a, st);
             else launch_stream<float, true>(nt, sw, grid, a, st);

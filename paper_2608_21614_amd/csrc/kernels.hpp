@@ -64,8 +64,7 @@ struct FfnArgs {
     float* off_w = nullptr;
     // bf16 prefill: the token rows gathered into the MFMA tile layout, ffn_gather_rows(s) x H
     void* xg = nullptr;
-    // prefill: the tiled kernels' tables (bf16: ffn_tile_meta_bytes(s); fp32: 32 + 24 bytes a
-    // group), 32-byte aligned, and
+    // prefill: the tiled kernels' tables (ffn_tile_meta_bytes(s), 16-byte aligned), and
     int32_t* tmeta = nullptr;
     int32_t* tclaim = nullptr;  // the tiled kernels' claim counters (ffn_tile_claim_bytes(s))
     // bf16 prefill: phase 2 writes the expert outputs here in bf16 ([rows][H]); without it the

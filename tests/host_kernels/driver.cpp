@@ -102,7 +102,8 @@ static void run(const Case& c) {
     // the prefill FFN's preparation, on buffers of the workspace's sizes
     std::fill(off_rows.get(), off_rows.get() + (size_t)P * H * elt, 0xEE);
     std::fill(off_w.get(), off_w.get() + P, -1.f);
-    const size_t meta_bytes = s.bf16 ? ffn_tile_meta_bytes(s) : (size_t)s.T * s.E * 4;
+    const size_t meta_bytes = ffn_tile_meta_bytes(s);
+    if (!s.bf16) CHECK(meta_bytes <= (size_t)s.T * s.E * 4, "the scores' room holds the tables");
     auto meta = filled<int32_t>(meta_bytes / 4, 0x5A5A5A5A), claim = filled<int32_t>(ffn_tile_claim_bytes(s) / 4, 77);
     auto xg = filled<uint16_t>((size_t)ffn_gather_rows(s) * H, 0xDEAD);
     FfnArgs a;

@@ -443,7 +443,7 @@ EDGE = [
     (40, 128, 256, 64, 8, 8, 64, "bf16", 256),
     (200, 128, 256, 64, 8, 8, 128, "bf16", 128),
     (24, 64, 16, 64, 8, 8, 64, "f32", 8),
-    # fp32 prefill on MFMA: groups of several 64-row chunks (one ragged), shared
+    # fp32 prefill on MFMA: groups of several 32-row items (one ragged), shared
     # experts wider than the routed ones, and more experts than resident slots
     (300, 256, 16, 192, 4, 2, 320, "f32", 10),
     (65, 128, 4, 64, 1, 1, 64, "f32", 4),
